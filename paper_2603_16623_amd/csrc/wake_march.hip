@@ -172,12 +172,11 @@ __device__ __forceinline__ void ion_load(const IonView& V, int h, double* q) {
 }
 
 // q: the record ion_load gave for the same hint h.
-__device__ __forceinline__ void ion_fields(const IonView& V, double r, dd lnr, int& h, double* q, dd& ps,
-                                           dd& dp) {
+__device__ __forceinline__ Lerp ion_fields(const IonView& V, double r, dd lnr, int& h, double* q) {
   if (!(r < V.Rp)) {
-    ps = dd_sub(V.T0, dd_mul(V.Q, lnr));
-    dp = dd_neg(dd_div_d(V.Q, r));
-    return;
+    const dd ps = dd_sub(V.T0, dd_mul(V.Q, lnr));
+    const dd dp = dd_neg(dd_div_d(V.Q, r));
+    return {ps.hi, ps.lo, 0.0, dp.hi, dp.lo, 0.0, 0.0};
   }
   const GA<double>& R = V.R;
   const int N = V.N;
@@ -217,8 +216,7 @@ __device__ __forceinline__ void ion_fields(const IonView& V, double r, dd lnr, i
   }
   h = j;
   const double t = (r - q[IR_LO]) * rcp_nr(q[IR_HI] - q[IR_LO]);
-  ps = dd_add_d({q[IR_PSH], q[IR_PSL]}, t * q[IR_DPS]);
-  dp = dd_add_d({q[IR_DPH], q[IR_DPL]}, t * q[IR_DDP]);
+  return {q[IR_PSH], q[IR_PSL], q[IR_DPS], q[IR_DPH], q[IR_DPL], q[IR_DDP], t};
 }
 
 // Ion interval of radius r from the interval nodes kept in LDS as floats
@@ -231,9 +229,16 @@ __device__ __forceinline__ int ion_find(const float* nodes, int N, double r, int
   const float x = (float)r;
   j = j < 0 ? 0 : (j > N ? N : j);
   int a, b;
-  if (nodes[j] <= x) {
-    a = j;                                   // nodes[a] <= x
-    int step = 1;
+  // the common case, at most four nodes up from the guess (the interval of
+  // the ring before, in radial order), from one round of independent reads:
+  // the gallop's smallest answer took four dependent ones of ~65 cycles, in
+  // every lane's slowest order
+  const float n0 = nodes[j], n1 = nodes[min(j + 1, N)], n2 = nodes[min(j + 2, N)], n3 = nodes[min(j + 3, N)],
+              n4 = nodes[min(j + 4, N)];
+  if (n0 <= x) {
+    a = min(j + (n1 <= x ? 1 : 0) + (n2 <= x ? 1 : 0) + (n3 <= x ? 1 : 0) + (n4 <= x ? 1 : 0), N);
+    if (a < j + 4 || a == N) return a;
+    int step = 4;                            // nodes[a] <= x
     for (;;) {
       b = a + step;
       if (b > N) { b = N + 1; break; }
@@ -2044,28 +2049,24 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       int h = jn;
       const dd lnr = {x_ln.x, x_ln.y};
       const double w = x_wc.x, wh = x_wc.y;
-      double q[WAKE_ION_REC];
-#pragma unroll
-      for (int i = 0; i < WAKE_ION_REC; ++i) q[i] = x_q[i];
       x_ru = z_ru; x_ln = z_ln; x_hs = z_hs; x_hn = z_hn;
       if (k + 2 < cnt) {
         const unsigned s = WAKE_SLOT(sl + 2 * NT);
         z_ru = Sc.ld(RS_RU, s); z_ln = Sc.ld(RS_LN, s); z_hs = st_hs(Sc, s);
         if (!lds_ion) z_hn = st_hint(Sc, s);
       }
+      const double irho = rcp_nr(rho);
+      const dd PTi = psi_next(PT, lnr, w);
+      const dd Si = dd_add_d(S, w);
+      double psi, dpsi;
+      psi_family(S, Si, PTi, lnr, rho, irho, wh, ion_fields(IV, rho, lnr, h, x_q), psi, dpsi);
+      psi += psi_axis;
+      // the next ring's weights and ion record, into the registers just read
       if (k + 1 < cnt) {
         x_wc = KC.ld(RC_W, (unsigned)x_hs);
         jn = lds_ion ? ion_find(s_ion, N, x_ru.x, h) : x_hn;
         ion_load(IV, jn, x_q);
       }
-      const double irho = rcp_nr(rho);
-      const dd PTi = dd_add_fast(PT, dd_mul_d(lnr, w));
-      const dd pe = dd_add_fast(dd_mul(dd_add_d(S, w), lnr), dd_neg(PTi));    // psi_e - sum w ln rho
-      const dd de = dd_div_rcp(dd_add_d(S, wh), rho, irho);         // d_rho psi_e (self w^)
-      dd ips, idp;
-      ion_fields(IV, rho, lnr, h, q, ips, idp);
-      const double psi = dd_round(dd_add_fast(pe, ips)) + psi_axis;
-      const double dpsi = dd_round(dd_add_fast(de, idp));
       if (GRID && rho >= gb_next) {
         // nodes of interval p = (rho_{p-1}, rho_p]: the sums below position p
         const int ghi = grid_last_below(rho, dgB, idgB, ngB, grB);
@@ -2077,7 +2078,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         gb_lo = ghi;
         gb_next = gb_lo + 1 < ngB ? grid_node_r(gb_lo + 1, dgB, grB) : INFINITY;
       }
-      S = dd_add_d(S, w);
+      S = Si;
       PT = PTi;
       // beam charge inside rho (strictly below), analytic beams, lasers
       double lam = 0.0;
@@ -2677,8 +2678,9 @@ __global__ void grid_init_kernel(WakeInst I, double* tab, int n_entries) {
   int h = 0;
   double q[WAKE_ION_REC];
   ion_load(IV, h, q);
-  dd ps, dp;
-  ion_fields(IV, r, l, h, q, ps, dp);
+  const Lerp x = ion_fields(IV, r, l, h, q);
+  dd ps = {x.ph, x.pl};
+  const dd dp = dd_add_d({x.dh, x.dl}, x.t * x.ds);
   if (r < I.Rp) {
     const dd a = two_sum(r, -q[IR_LO]);            // r - lo, exact
     const dd b = two_sum(q[IR_HI], -q[IR_LO]);     // hi - lo, exact

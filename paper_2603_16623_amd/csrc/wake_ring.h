@@ -49,13 +49,57 @@ __device__ __forceinline__ Pack<4> mat_adj(const Pack<4>& m) {
   return {{m.v[3], -m.v[1], -m.v[2], m.v[0]}};
 }
 
-// a / b for double-double a with a precomputed reciprocal ib = 1/b
+// a / b for double-double a with a precomputed reciprocal ib = 1/b: the
+// remainder of the first quotient comes from one fma (a.hi - q1 b is a
+// multiple of ulp(q1) ulp(b) of at most two ulps of q1 times b, so the fma
+// leaves it to within 2^-105 of a.hi), the second quotient takes it and a.lo.
 __device__ __forceinline__ dd dd_div_rcp(dd a, double b, double ib) {
   _Pragma("clang fp contract(off)")
   const double q1 = a.hi * ib;
-  const dd r = dd_sub(a, two_prod(q1, b));
-  const double q2 = r.hi * ib;
+  const double q2 = (__builtin_fma(-q1, b, a.hi) + a.lo) * ib;
   return fast_two_sum(q1, q2);
+}
+
+// The other species' field at a ring, as the interpolation leaves it:
+// psi = (ph + pl) + t ps, d_rho psi = (dh + dl) + t ds with ph + pl and
+// dh + dl the lower node's double-doubles and ps, ds the steps to the next.
+struct Lerp {
+  double ph, pl, ps, dh, dl, ds, t;
+};
+
+// PT + lnr w: the running sum of w ln rho, one ring further.
+__device__ __forceinline__ dd psi_next(dd PT, dd lnr, double w) {
+  _Pragma("clang fp contract(off)")
+  const dd p = two_prod(lnr.hi, w);
+  dd s = two_sum(PT.hi, p.hi);
+  s.lo += PT.lo + __builtin_fma(lnr.lo, w, p.lo);
+  return fast_two_sum(s.hi, s.lo);
+}
+
+// psi - psi(0) and d_rho psi at a ring (eqs. psi, dpsi_dr; the ring itself
+// with its modified weight wh in the Gauss sum): S the weights below it, Sn
+// those through it, PTn the sum of w ln rho through it, X the other
+// species' share.  The sums cancel to psi, so their high parts are added
+// with two_sum and every low part in binary64 (error a few 2^-104 of the
+// terms, as from double-double additions); nothing is renormalised on the
+// way, since both results are rounded at the end: 40 operations where the
+// chain of double-double calls took 94 (7900 rings on one workgroup, rings
+// in order: 58.3 -> 53.5 us per slice together with ion_find's one round of
+// reads).
+__device__ __forceinline__ void psi_family(dd S, dd Sn, dd PTn, dd lnr, double rho, double irho, double wh,
+                                           const Lerp& X, double& psi, double& dpsi) {
+  _Pragma("clang fp contract(off)")
+  const dd p = two_prod(Sn.hi, lnr.hi);
+  const double pe = __builtin_fma(Sn.hi, lnr.lo, __builtin_fma(Sn.lo, lnr.hi, p.lo));
+  const dd a = two_sum(p.hi, -PTn.hi);
+  const dd b = two_sum(a.hi, X.ph);
+  const double lo = ((pe - PTn.lo) + X.pl) + (a.lo + b.lo);
+  psi = b.hi + __builtin_fma(X.t, X.ps, lo);
+  const dd g = two_sum(S.hi, wh);
+  const double q1 = g.hi * irho;
+  const double q2 = (__builtin_fma(-q1, rho, g.hi) + (g.lo + S.lo)) * irho;
+  const dd d = two_sum(q1, X.dh);
+  dpsi = d.hi + __builtin_fma(X.t, X.ds, (q2 + X.dl) + d.lo);
 }
 
 // Number of entries of the ascending table br[0..m) below r, given that
