@@ -44,6 +44,46 @@
 
 namespace {
 
+struct IonsLocal {
+  double pb, ipb, gm, v, A;
+};
+
+// psibar, 1/psibar, gamma (eq. motion_4), v = w u/(rho psibar), A_i
+__device__ __forceinline__ IonsLocal ions_local(double irho, double u, double w, double psi, double a2) {
+  IonsLocal L;
+  L.pb = 1.0 + psi;
+  L.ipb = rcp_nr(L.pb);
+  L.gm = (1.0 + u * u + L.pb * L.pb + 0.5 * a2) * (0.5 * L.ipb);
+  L.v = w * u * irho * L.ipb;
+  L.A = w * irho * L.ipb;
+  return L;
+}
+
+// B_i and C_i of eqs. b_coeffs_2-3 for an electron ring (q=-1, m=1)
+__device__ __forceinline__ void ring_BC(double irho, double u, double w, const IonsLocal& L, double dpsi,
+                                        double dz, double bb, double da2, double& B, double& C) {
+  const double wr = w * irho;
+  const double ipb2 = L.ipb * L.ipb;
+  const double u2 = u * u;
+  B = -wr * L.gm * dpsi * ipb2 + wr * bb * L.ipb + 0.25 * wr * da2 * ipb2 + wr * irho * u2 * ipb2 +
+      wr * u2 * dpsi * ipb2 * L.ipb - wr * u * dz * ipb2;
+  C = -wr * (L.gm * L.ipb - 1.0) + wr * u2 * ipb2;
+}
+
+// offset s_i of eq. ai_bi
+__device__ __forceinline__ void rec_offset(double A, double B, double C, double rho, double& sa,
+                                          double& sb) {
+  sa = (2.0 * B + A * C) * 0.25;
+  sb = rho * (4.0 * C - 2.0 * B * rho - A * C * rho) * 0.25;
+}
+
+// transfer matrix M_i of eq. ai_bi (det M_i = 1)
+__device__ __forceinline__ Pack<4> rec_matrix(double A, double rho, double irho) {
+  const double h = 0.5 * A * rho;
+  return {{1.0 + h, 0.5 * A * irho, -h * rho * rho, 1.0 - h}};
+}
+
+
 constexpr int NT = WAKE_IONS_NT;
 constexpr int NW = NT / 64;
 constexpr int NMAX = WAKE_IONS_NMAX;
@@ -627,7 +667,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
           const double irho = rcp_nr(r);
           const double a2 = has_laser ? wk[IW_A2 * S + sl] : 0.0;
           const double da2 = has_laser ? wk[IW_DA2 * S + sl] : 0.0;
-          const Local L = local_of(irho, wk[IW_U * S + sl], w, wk[IW_PSI * S + sl], a2);
+          const IonsLocal L = ions_local(irho, wk[IW_U * S + sl], w, wk[IW_PSI * S + sl], a2);
           double B, Cc, sa, sb;
           ring_BC(irho, wk[IW_U * S + sl], w, L, wk[IW_DPSI * S + sl], dz, wk[IW_BB * S + sl], da2, B,
                   Cc);

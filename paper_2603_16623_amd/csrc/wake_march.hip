@@ -2106,20 +2106,24 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       const double bb = lam * irho;
       const Local L = local_of(irho, u, w, psi, aa);
       if (!(L.pb > 0.0)) bad = 1.0;
-      G = mat_mul(rec_matrix(L.A, rho, irho), G);
-      Vw += L.v;
-      // s_i with d_zeta psi = (Vw - own) + c: s = s0 + c s1
-      const double dz0 = Vw - (w - wh) * u * irho * L.ipb;
-      double B0, Cc;
-      ring_BC(irho, u, w, L, dpsi, dz0, bb, dda, B0, Cc);
-      const double beta = w * irho * u * L.ipb * L.ipb;     // -dB/d(d_zeta psi)
-      double s0a, s0b;
-      rec_offset(L.A, B0, Cc, rho, s0a, s0b);
-      const double s1a = -0.5 * beta, s1b = 0.5 * rho * rho * beta;
-      l0a += G.v[0] * s0b - G.v[2] * s0a;
-      l0b += G.v[1] * s0b - G.v[3] * s0a;
-      l1a += G.v[0] * s1b - G.v[2] * s1a;
-      l1b += G.v[1] * s1b - G.v[3] * s1a;
+      // s_i with d_zeta psi = (sum of v inside the chunk before the ring + w^
+      // share) + c: s_a = s0 - c beta / 2
+      const double dz0 = __builtin_fma(wh, L.cu, Vw);
+      Vw = __builtin_fma(w, L.cu, Vw);
+      double cc, s0;
+      ring_source(irho, u, w, L, aa, dpsi, dz0, bb, dda, cc, s0);
+      const double hbeta = 0.5 * L.A * u * L.ipb;          // beta = -dB/d(d_zeta psi)
+      const double r2 = rho * rho, hAi = 0.5 * L.A * irho, rC = 0.5 * w * cc;
+      const double m0 = __builtin_fma(r2, G.v[0], G.v[2]), m1 = __builtin_fma(r2, G.v[1], G.v[3]);
+      const double y0 = hAi * m0, y1 = hAi * m1;
+      G.v[0] += y0;
+      G.v[1] += y1;
+      G.v[2] = __builtin_fma(-r2, y0, G.v[2]);
+      G.v[3] = __builtin_fma(-r2, y1, G.v[3]);
+      l0a = __builtin_fma(-s0, m0, __builtin_fma(G.v[0], rC, l0a));
+      l0b = __builtin_fma(-s0, m1, __builtin_fma(G.v[1], rC, l0b));
+      l1a = __builtin_fma(hbeta, m0, l1a);
+      l1b = __builtin_fma(hbeta, m1, l1b);
       SCR.st(SC_PSI, goff + sl, d2(psi, dpsi));
       if (has_laser) { A2.st(goff + sl, aa); DA2.st(goff + sl, dda); }
       // the ring's interval: its hint at the next slice (the thread's first
@@ -2343,20 +2347,22 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         if (s_misc[3 * si] == 2.0) lam += s_misc[3 * si + 1] * (-expm1(-rho * rho * s_misc[3 * si + 2]));
       const double bb = lam * irho;
       const Local L = local_of(irho, u, w, psi, a2);
-      const double dz = -(Vgt + (w - wh) * u * irho * L.ipb);
-      double B, Cc;
-      ring_BC(irho, u, w, L, dpsi, dz, bb, da2, B, Cc);
-      double sa, sb;
-      rec_offset(L.A, B, Cc, rho, sa, sb);
-      D += sa * hb - sb * ha;                              // D_{i-1} (det[s_i, h_i])
-      E -= ga * sb - gb * sa;                              // E_{i-1} (det[g_i, s_i])
-      const double hh = 0.5 * L.A * rho, q = 0.5 * L.A * irho, pp = hh * rho * rho;
-      const double nga = (1.0 - hh) * ga - q * gb, ngb = pp * ga + (1.0 + hh) * gb;   // M_i^-1 g_i
-      const double nha = (1.0 - hh) * ha - q * hb, nhb = pp * ha + (1.0 + hh) * hb;   // M_i^-1 h_i
-      ga = nga; gb = ngb; ha = nha; hb = nhb;
-      const double a = (ha * E - ga * D) * iW;
-      const double b = (hb * E - gb * D) * iW;
-      const double bp = a * rho + b * irho + wh * rcp_nr(w) * Cc;
+      const double Vn = __builtin_fma(w, L.cu, Vgt);       // sum of v from this ring on
+      const double dz = __builtin_fma(wh, L.cu, -Vn);
+      double cc, sa;
+      ring_source(irho, u, w, L, a2, dpsi, dz, bb, da2, cc, sa);
+      const double r2 = rho * rho, hAi = 0.5 * L.A * irho, rC = 0.5 * w * cc;
+      const double mg = __builtin_fma(r2, ga, gb), mh = __builtin_fma(r2, ha, hb);
+      D = __builtin_fma(sa, mh, __builtin_fma(-rC, ha, D));    // D_{i-1} (det[s_i, h_i])
+      E = __builtin_fma(sa, mg, __builtin_fma(-rC, ga, E));    // E_{i-1} (det[g_i, s_i])
+      const double yg = hAi * mg, yh = hAi * mh;               // g, h of interval i-1
+      ga -= yg;
+      gb = __builtin_fma(r2, yg, gb);
+      ha -= yh;
+      hb = __builtin_fma(r2, yh, hb);
+      // a_{i-1} rho + b_{i-1} / rho from x_{i-1} = (h E - g D) / W, and the
+      // ring's own share w^ C / w
+      const double bp = irho * __builtin_fma(iW, __builtin_fma(E, mh, -(D * mg)), 0.5 * wh * cc);
       const double bt = bb + bp;
       const double ez = -dz;
       if (!(isfinite(psi) && isfinite(dpsi) && isfinite(ez) && isfinite(bt))) bad = 1.0;
@@ -2375,11 +2381,11 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       }
       if (do_push) {
         const double f_r = u * L.ipb;
-        const double f_u = L.gm * dpsi * L.ipb - bt - 0.25 * da2 * L.ipb;
+        const double f_u = __builtin_fma(L.ipb, __builtin_fma(L.gm, dpsi, -0.25 * da2), -bt);
         double pr = f_r, pu = f_u;
         if (n > 0) { pr = fr_p; pu = fu_p; }
-        double rn = rho + dxi * (1.5 * f_r - 0.5 * pr);
-        double un = u + dxi * (1.5 * f_u - 0.5 * pu);
+        double rn = __builtin_fma(dxi, __builtin_fma(1.5, f_r, -0.5 * pr), rho);
+        double un = __builtin_fma(dxi, __builtin_fma(1.5, f_u, -0.5 * pu), u);
         double sr = f_r, su = f_u;
         if (rn < 0.0) { rn = -rn; un = -un; sr = -sr; su = -su; }
         if (!(isfinite(rn) && isfinite(un))) bad = 1.0;
@@ -2398,7 +2404,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         nxt_r = rn;
         nxt_i = id;
       }
-      Vgt += L.v;
+      Vgt = Vn;
       if (GRID) {
         if (CHI && chi) {
           const double c = w * L.ipb;
@@ -2409,6 +2415,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         if (rlo < ge_top) {
           // nodes of interval p = (rho_{p-1}, rho_p]
           const int glo = GN.last_below(rlo) + 1;
+          const double a = (ha * E - ga * D) * iW, b = (hb * E - gb * D) * iW;
           #pragma unroll 1
           for (int g = glo; g <= ge_hi; ++g) {
             gscr[GS * g + 2] = d2(Vgt, a);
