@@ -771,6 +771,37 @@ static int copy_out(double* dst, const double* src, size_t n, int dev, hipStream
   return WAKE_OK;
 }
 
+// Rows q (N doubles each, one after the other at base) to outs[q], null ones
+// skipped.  Device memory: one kernel.  Host memory: one transfer of all rows
+// and a host copy each while they are short (a transfer to pageable memory
+// costs some 10 us whatever its size: six of them were most of a small solve's
+// read-out), a transfer per row beyond.
+static const size_t kRowsOnce = 8192;
+static int read_rows(const double* base, size_t N, double* const* outs, int rows, int dev, hipStream_t s) {
+  if (dev) {
+    HIP_TRY(launch_rows_out(base, N, outs, rows, s));
+    return WAKE_OK;
+  }
+  int wanted = 0;
+  for (int q = 0; q < rows; ++q) wanted += outs[q] != nullptr;
+  double* tmp = N <= kRowsOnce && wanted > 1 ? new (std::nothrow) double[N * rows] : nullptr;
+  if (tmp) {
+    hipError_t e = hipMemcpyAsync(tmp, base, sizeof(double) * N * rows, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess)
+      for (int q = 0; q < rows; ++q)
+        if (outs[q]) std::memcpy(outs[q], tmp + q * N, sizeof(double) * N);
+    delete[] tmp;
+    HIP_TRY(e);
+    return WAKE_OK;
+  }
+  for (int q = 0; q < rows; ++q) {
+    const int r = copy_out(outs[q], base + q * N, N, dev, s);
+    if (r != WAKE_OK) return r;
+  }
+  return WAKE_OK;
+}
+
 // Recorded fields of one species (snapshots snap, last slice last).
 static int fields_of(wake_ctx* c, const double* snap, const double* last, int32_t slice, double* psi,
                      double* erbt, double* ez, double* bt, double* rho, double* ur, int32_t dev) {
@@ -793,10 +824,8 @@ static int fields_of(wake_ctx* c, const double* snap, const double* last, int32_
   }
   const size_t N = I.N;
   double* outs[OUT_N] = {psi, erbt, ez, bt, rho, ur};
-  for (int q = 0; q < OUT_N; ++q) {
-    r = copy_out(outs[q], base + q * N, N, dev, c->stream);
-    if (r != WAKE_OK) return r;
-  }
+  r = read_rows(base, N, outs, OUT_N, dev, c->stream);
+  if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return WAKE_OK;
 }
@@ -1027,10 +1056,8 @@ extern "C" int wake_grid_fields(wake_ctx* c, int32_t slice, double* psi, double*
   grid_slice(c, slice, &first, &ng);
   const double* base = I.grid + 5 * first;
   double* outs[4] = {psi, erbt, ez, bt};
-  for (int q = 0; q < 4; ++q) {
-    r = copy_out(outs[q], base + q * ng, ng, dev, c->stream);
-    if (r != WAKE_OK) return r;
-  }
+  r = read_rows(base, ng, outs, 4, dev, c->stream);
+  if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return WAKE_OK;
 }
@@ -1069,19 +1096,33 @@ extern "C" int wake_grid_chi(wake_ctx* c, int32_t slice, double* chi, int32_t de
   return WAKE_OK;
 }
 
+// The axis values sit on the device as (psi, E_z) pairs per slice: split by a
+// kernel (device memory) or on the host after one transfer.  (Two strided
+// copies of 8-B rows took 7 us a row and copy: 16 ms for 1200 slices, as long
+// as a 1000-ring march through them; the transfer and the split take 30 us.)
 extern "C" int wake_lineout(wake_ctx* c, double* psi_axis, double* ez_axis, int32_t dev) {
   if (!c) return WAKE_EINVAL;
   int r = drain(c);
   if (r != WAKE_OK) return r;
-  const hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   const size_t n = c->I.n_xi;
-  if (psi_axis)
-    HIP_TRY(hipMemcpy2DAsync(psi_axis, sizeof(double), c->I.axis, 2 * sizeof(double), sizeof(double),
-                             n, kind, c->stream));
-  if (ez_axis)
-    HIP_TRY(hipMemcpy2DAsync(ez_axis, sizeof(double), c->I.axis + 1, 2 * sizeof(double),
-                             sizeof(double), n, kind, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  if (!psi_axis && !ez_axis) return WAKE_OK;
+  if (dev) {
+    HIP_TRY(launch_axis_out(c->I.axis, n, psi_axis, ez_axis, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return WAKE_OK;
+  }
+  double* tmp = new (std::nothrow) double[2 * n];
+  if (!tmp) return WAKE_ENOMEM;
+  hipError_t e = hipMemcpyAsync(tmp, c->I.axis, sizeof(double) * 2 * n, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) {
+    if (psi_axis)
+      for (size_t i = 0; i < n; ++i) psi_axis[i] = tmp[2 * i];
+    if (ez_axis)
+      for (size_t i = 0; i < n; ++i) ez_axis[i] = tmp[2 * i + 1];
+  }
+  delete[] tmp;
+  HIP_TRY(e);
   return WAKE_OK;
 }
 
@@ -1099,10 +1140,8 @@ static int get_state_of(wake_ctx* c, int sp, int32_t* slice, double* rho, double
   else
     HIP_TRY(launch_state_by_id(c->I, st, st + N, st + 2 * N, st + 3 * N, c->stream));
   double* outs[4] = {rho, ur, f_rho, f_u};
-  for (int q = 0; q < 4; ++q) {
-    r = copy_out(outs[q], st + q * N, N, dev, c->stream);
-    if (r != WAKE_OK) return r;
-  }
+  r = read_rows(st, N, outs, 4, dev, c->stream);
+  if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (slice) *slice = next;
   return WAKE_OK;

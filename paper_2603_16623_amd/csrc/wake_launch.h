@@ -23,6 +23,10 @@ hipError_t launch_state_by_id(const WakeInst& I, double* rho, double* u, double*
 hipError_t launch_state_set(const WakeInst& I, const double* rho, const double* u, const double* fr,
                             const double* fu, int slice, hipStream_t s);
 hipError_t launch_reset(const WakeInst* d_insts, int n_insts, hipStream_t s);
+// rows (at most 6) of n doubles, one after the other at src, to dst[q] (device
+// memory; null: skipped); axis pairs (psi, E_z) of n slices to two arrays
+hipError_t launch_rows_out(const double* src, size_t n, double* const* dst, int rows, hipStream_t s);
+hipError_t launch_axis_out(const double* axis, size_t n, double* psi, double* ez, hipStream_t s);
 hipError_t launch_ctl_gather(const WakeInst* d_insts, int n, int32_t* out, hipStream_t s);
 
 // marcher: workgroups of nt threads (256 or 512)

@@ -50,6 +50,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 // A per-instance array seen as uniform: its base in scalar registers and in
 // the global address space, indexed with 32-bit element offsets (loads and
 // stores then take the scalar-base + vector-offset form).
@@ -2646,6 +2648,33 @@ __global__ void ctl_gather_kernel(const WakeInst* __restrict__ insts, int n, int
 // ---------------------------------------------------------------------------
 // host-callable launchers
 // ---------------------------------------------------------------------------
+struct RowsOut {
+  double* q[OUT_N];
+};
+__global__ void rows_out_kernel(const double* __restrict__ src, size_t n, RowsOut dst) {
+  double* const d = dst.q[blockIdx.y];
+  if (!d) return;
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+    d[i] = src[blockIdx.y * n + i];
+}
+__global__ void axis_out_kernel(const double* __restrict__ axis, size_t n, double* psi, double* ez) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    if (psi) psi[i] = axis[2 * i];
+    if (ez) ez[i] = axis[2 * i + 1];
+  }
+}
+static unsigned out_blocks(size_t n) { return (unsigned)std::min<size_t>(std::max<size_t>((n + 255) / 256, 1), 1024); }
+hipError_t launch_rows_out(const double* src, size_t n, double* const* dst, int rows, hipStream_t s) {
+  RowsOut o = {};
+  for (int q = 0; q < rows && q < OUT_N; ++q) o.q[q] = dst[q];
+  hipLaunchKernelGGL(rows_out_kernel, dim3(out_blocks(n), rows), dim3(256), 0, s, src, n, o);
+  return hipGetLastError();
+}
+hipError_t launch_axis_out(const double* axis, size_t n, double* psi, double* ez, hipStream_t s) {
+  hipLaunchKernelGGL(axis_out_kernel, dim3(out_blocks(n)), dim3(256), 0, s, axis, n, psi, ez);
+  return hipGetLastError();
+}
+
 hipError_t launch_ctl_gather(const WakeInst* d_insts, int n, int32_t* out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(ctl_gather_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_insts, n, out);
