@@ -390,13 +390,12 @@ extern "C" int wake_create_mobile_ions(wake_ctx** out, const wake_plasma* plasma
       if (e != hipSuccess) { A.base = nullptr; release(c); return dev_err(e); }
       A.size = bytes;
     }
-    J.cst = A.take<double>((size_t)IK_N * N);
-    for (int b = 0; b < 2; ++b) J.st[b] = A.take<double>((size_t)2 * IS_N * N);
-    J.ord = A.take<int32_t>((size_t)2 * N);
+    J.cst = A.take<double>((size_t)IK_DOUBLES * S);
+    for (int b = 0; b < 2; ++b) J.st[b] = A.take<double>((size_t)2 * IS_N * 2 * S);
+    J.ord = A.take<int32_t>(2 * S);
     J.sid = A.take<int32_t>(2 * S);
     J.jx = A.take<int32_t>(2 * S);
-    J.tab = A.take<double>((size_t)2 * IT_N * S);
-    J.work = A.take<double>((size_t)2 * IW_N * S);
+    J.work = A.take<double>((size_t)2 * IW_N * 2 * S);
     J.axis = A.take<double>(2 * (size_t)I.n_xi);
     for (int sp = 0; sp < 2; ++sp) {
       J.snap[sp] = n_rec ? A.take<double>(n_rec * OUT_N * N) : nullptr;

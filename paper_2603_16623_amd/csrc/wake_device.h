@@ -24,6 +24,38 @@ __device__ __forceinline__ const WAKE_GLOBAL T* as_global(const T& x) {
   return (const WAKE_GLOBAL T*)&x;
 }
 
+// A per-instance array seen as uniform: its base in scalar registers and in
+// the global address space, indexed with 32-bit element offsets (loads and
+// stores then take the scalar-base + vector-offset form).
+template <class T>
+struct GA {
+  WAKE_GLOBAL T* p;
+  __device__ __forceinline__ T operator[](uint32_t i) const {
+    return *reinterpret_cast<WAKE_GLOBAL T*>(reinterpret_cast<WAKE_GLOBAL char*>(p) +
+                                            i * (uint32_t)sizeof(T));
+  }
+  __device__ __forceinline__ void st(uint32_t i, T v) const {
+    *reinterpret_cast<WAKE_GLOBAL T*>(reinterpret_cast<WAKE_GLOBAL char*>(p) +
+                                     i * (uint32_t)sizeof(T)) = v;
+  }
+};
+template <class T>
+__device__ __forceinline__ GA<T> uview(const T* q) {
+  const uint64_t v = reinterpret_cast<uint64_t>(q);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  GA<T> g;
+  g.p = reinterpret_cast<WAKE_GLOBAL T*>(((uint64_t)hi << 32) | lo);
+  return g;
+}
+// 16-B chunk of a record (two doubles), moved by one 16-B load or store.
+typedef double D2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ D2 d2(double x, double y) {
+  D2 r;
+  r.x = x;
+  r.y = y;
+  return r;
+}
 // ---------------------------------------------------------------------------
 // double-double (unevaluated sum hi + lo) arithmetic.  Contraction of a
 // multiply into an addition is forbidden inside every helper: after

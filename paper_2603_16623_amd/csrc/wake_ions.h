@@ -10,28 +10,30 @@
 #define WAKE_IONS_NT 1024      // workgroup threads of the two-species marcher
 #define WAKE_IONS_NMAX 8192    // rings per species (the sorted radii of both species sit in LDS)
 
-// per-ring constants by ring id (both species start at the same radii with
-// the same weights): w, w^, r0, 1/r0, ln r0 (dd), dr
-enum { IK_W = 0, IK_WH, IK_R0, IK_IR0, IK_LNH, IK_LNL, IK_DR, IK_N };
-// ring state planes by ring id: rho, u_r, and the Adams-Bashforth history
-enum { IS_RHO = 0, IS_U, IS_FR, IS_FU, IS_N };
-// node tables of a species by slot: its own psi (dd), d_rho psi (dd) and
-// d_zeta psi at its rings; B^(p) at the electron rings
-enum { IT_PSH = 0, IT_PSL, IT_DPH, IT_DPL, IT_DZ, IT_BP, IT_N };
-// per-position work by slot: the ring's weights and momentum gathered at
-// the slice head (w, w^, u_r), the fields (total of both species), psibar,
-// the beam field, the laser's |a|^2 and its gradient (with a laser only);
-// for the electrons the recursion's A_i, C_i, offset s_i, growing mode g
-// before ring i and the det-sum E before it.  ln rho, gamma and the
-// interpolation parameters are formed again where they are used.
-enum { IW_W = 0, IW_WH, IW_U, IW_PSI, IW_DPSI, IW_DZ, IW_BT, IW_PB, IW_BB, IW_A2, IW_DA2, IW_A, IW_C,
-       IW_SA, IW_SB, IW_GA, IW_GB, IW_E, IW_N };
+// All per-ring arrays are planes of 16-B chunks (two doubles), S = 1024 C
+// chunks each, so that a wave moves one chunk of 64 consecutive slots as
+// contiguous lanes.  Position p's slot is (p % C) * 1024 + p / C; ring id i's
+// home slot is the slot of position i, and the constants and the state sit
+// there: while rings keep roughly their initial order, their gathers touch
+// neighbouring slots (by ring id every lane read a line of its own, one a
+// cycle, and that was most of the march's time).
+//
+// constants by home slot (both species start at the same radii with the
+// same weights): (w, w^), (r0, 1/r0), ln r0 (dd), then a plane of 8-B dr
+enum { IK_W = 0, IK_R0, IK_LN, IK_DR, IK_DOUBLES = 7 };
+// ring state by home slot: (rho, u_r) and the Adams-Bashforth history
+enum { IS_RU = 0, IS_F, IS_N };
+// per-position work of one species by slot: (w, w^); ln rho (dd); its node
+// tables psi (dd), d_rho psi (dd), and (d_zeta psi, B^(p) at the electron
+// rings); the fields (psi, d_rho psi) of both species together; (u_r, q u /
+// (rho psibar)); (beam field, -); the laser's (|a|^2, gradient), with a laser
+// only; for the electrons (A_i, s_a) of the recursion and (d_zeta psi, cc)
+enum { IW_W = 0, IW_LN, IW_T0, IW_T1, IW_ZB, IW_F, IW_UC, IW_BB, IW_A2, IW_E, IW_DC, IW_N };
 
 // One two-species instance as the kernels see it.  All pointers are device
 // pointers.  Species 0 are the electrons (q = -1, m = 1), species 1 the
 // ions (q = +1, m = m_i).  Per species, thread t of the workgroup owns the
-// C = ceil(N / 1024) consecutive sorted positions [tC, tC + C); position p
-// is stored at slot (p % C) * 1024 + p / C (S = 1024 C slots per plane).
+// C = ceil(N / 1024) consecutive sorted positions [tC, tC + C).
 struct WakeIons {
   int32_t N, n_xi, first, count, stride, C;
   int32_t nb, n_an, has_laser, pad;
@@ -39,14 +41,13 @@ struct WakeIons {
   WakeAnalytic an[WAKE_MAX_ANALYTIC];
   const int32_t* boff;        // beam table (CSR over slices)
   const double *br, *bcum;
-  const double* cst;          // [IK_N][N]
-  double* st[2];              // two buffers, each [2 species][IS_N][N]
-  int32_t* ord;               // [2][N] ring ids in the latest sorted order (by position)
-  int32_t* sid;               // [2][S] ring id of each position, by slot
+  const double* cst;          // [IK_DOUBLES][S]
+  double* st[2];              // two buffers, each [2 species][IS_N][S] chunks
+  int32_t* ord;               // [2][S] ring ids in the latest sorted order, by slot
+  int32_t* sid;               // [2][S] home slot of the ring at each position, by slot
   int32_t* jx;                // [2][S] rings of the other species below each ring (-1: beyond
                               //        its edge), by slot
-  double* tab;                // [2][IT_N][S]
-  double* work;               // [2][IW_N][S]
+  double* work;               // [2 species][IW_N][S] chunks
   double* axis;               // [n_xi][2]: psi(0), E_z(0)
   double* snap[2];            // per species [n_rec][OUT_N][N] by ring id
   double* last[2];            // per species [OUT_N][N]: the last marched slice

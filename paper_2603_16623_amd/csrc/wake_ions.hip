@@ -8,33 +8,41 @@
 // One workgroup of 1024 threads marches one instance through its slices.
 // Per species, thread t owns the C = ceil(N / 1024) consecutive sorted
 // positions [tC, tC + C); per-position arrays are stored by slot
-// (p % C) * 1024 + p / C, so the k-th positions of a wave are contiguous.
-// The sorted radii of both species sit in LDS, where the interval searches
-// of the gathers run; node tables, per-position work and ring state live in
-// device memory.
+// (p % C) * 1024 + p / C and per-ring ones by the slot of the ring's initial
+// position, so the k-th positions of a wave are contiguous.  The sorted radii
+// of both species sit in LDS (by position, the low bits exchanged so that
+// lanes C apart meet different banks), where the interval searches of the
+// gathers run; node tables, per-position work and ring state live in device
+// memory as planes of 16-B chunks.
+//
+// What bounds it: with one instance the chain of phases (a barrier and a
+// round of loads each), with a device full of instances the bytes of the
+// planes.  Before the planes, constants, state and order were read by ring id
+// or position, one line per lane: 256 cycles of the load path per wave for
+// the four constants of ln rho alone.
 //
 // Per slice:
 //   order    each species' (rho, id) order: the previous one if it still
 //            holds, else rounds of wave blocks of 256 positions sorted in
 //            LDS and the blocks between them merged (the bitonic network
 //            over all positions after three rounds that leave disorder);
-//   sums     own psi and d_rho psi at each species' rings (eqs. psi,
+//   sums     ln rho and the chunk sums of w and w ln rho; after their scans
+//            own psi and d_rho psi at each species' rings (eqs. psi,
 //            dpsi_dr; double-double prefix of w and suffix of w ln rho, the
 //            ring itself with w^), its axis value, outer edge and exterior
 //            field: the node tables;
 //   gather   the other species' psi and d_rho psi interpolated at every
-//            ring; psibar and gamma with the species' q and m (eq.
-//            plasma_particle_motion_4); beam and laser sources; own d_zeta
-//            psi (eq. dpsi_dzeta, suffix of q w u / (rho psibar)), then the
-//            other species' interpolated;
-//   B^(p)    electrons only: A, B, C (eqs. b_coeffs_1-3), the two-point
-//            recursion (eq. ai_bi) in Green's-function form (growing mode g,
-//            decaying mode h, W = det[g, h], x_i = (h_i E_i - g_i D_i) / W)
-//            and B^(p) at the electron rings (eq. b_theta_plasma); the ions
-//            take it interpolated between the electron rings;
-//   push     fields out, Adams-Bashforth-2 push (eqs.
-//            plasma_particle_motion_1-2) of both species with their q and m,
-//            reflection through the axis, into the other state buffer.
+//            ring; psibar with the species' q and m; beam and laser sources;
+//            own d_zeta psi (eq. dpsi_dzeta, suffix of q w u / (rho psibar));
+//   B^(p)    electrons only, forward: the ions' d_zeta psi interpolated, the
+//            ring's offset and transfer (eqs. b_coeffs_1-3, ai_bi), the
+//            chunk's product G and lambda = sum of G_i^T J s_i; scans of the
+//            transfers and then of the det-sums g.lambda, h.lambda (the
+//            one-species marcher's Green's-function form);
+//   push     electrons, backward: g and h stepped back, B^(p) (eq.
+//            b_theta_plasma), fields out, Adams-Bashforth-2 push into the
+//            other state buffer; then the ions: d_zeta psi and B^(p)
+//            interpolated between the electron rings, fields out, push.
 #include "wake_common.h"
 #include "wake_device.h"
 #include "wake_ring.h"
@@ -43,46 +51,6 @@
 #include <math.h>
 
 namespace {
-
-struct IonsLocal {
-  double pb, ipb, gm, v, A;
-};
-
-// psibar, 1/psibar, gamma (eq. motion_4), v = w u/(rho psibar), A_i
-__device__ __forceinline__ IonsLocal ions_local(double irho, double u, double w, double psi, double a2) {
-  IonsLocal L;
-  L.pb = 1.0 + psi;
-  L.ipb = rcp_nr(L.pb);
-  L.gm = (1.0 + u * u + L.pb * L.pb + 0.5 * a2) * (0.5 * L.ipb);
-  L.v = w * u * irho * L.ipb;
-  L.A = w * irho * L.ipb;
-  return L;
-}
-
-// B_i and C_i of eqs. b_coeffs_2-3 for an electron ring (q=-1, m=1)
-__device__ __forceinline__ void ring_BC(double irho, double u, double w, const IonsLocal& L, double dpsi,
-                                        double dz, double bb, double da2, double& B, double& C) {
-  const double wr = w * irho;
-  const double ipb2 = L.ipb * L.ipb;
-  const double u2 = u * u;
-  B = -wr * L.gm * dpsi * ipb2 + wr * bb * L.ipb + 0.25 * wr * da2 * ipb2 + wr * irho * u2 * ipb2 +
-      wr * u2 * dpsi * ipb2 * L.ipb - wr * u * dz * ipb2;
-  C = -wr * (L.gm * L.ipb - 1.0) + wr * u2 * ipb2;
-}
-
-// offset s_i of eq. ai_bi
-__device__ __forceinline__ void rec_offset(double A, double B, double C, double rho, double& sa,
-                                          double& sb) {
-  sa = (2.0 * B + A * C) * 0.25;
-  sb = rho * (4.0 * C - 2.0 * B * rho - A * C * rho) * 0.25;
-}
-
-// transfer matrix M_i of eq. ai_bi (det M_i = 1)
-__device__ __forceinline__ Pack<4> rec_matrix(double A, double rho, double irho) {
-  const double h = 0.5 * A * rho;
-  return {{1.0 + h, 0.5 * A * irho, -h * rho * rho, 1.0 - h}};
-}
-
 
 constexpr int NT = WAKE_IONS_NT;
 constexpr int NW = NT / 64;
@@ -108,25 +76,37 @@ static_assert(IonsLds::bytes <= 160 * 1024, "two-species LDS");
 enum { SC_PAH = 0, SC_PAL, SC_QH, SC_QL, SC_EDGE, SC_EPH, SC_EPL, SC_EDP, SC_EDL, SC_DZH, SC_DZL,
        SC_N = 16 };
 
-__device__ __forceinline__ unsigned pslot(int p, int C) { return (unsigned)((p % C) * NT + p / C); }
+// Slot of position p (home slot of ring p): p / C as a multiply and shift,
+// exact for p < 8192 and C <= 8 (div = 65536 / C rounded up).
+__device__ __forceinline__ unsigned pslot(int p, int C, unsigned div) {
+  const unsigned q = ((unsigned)p * div) >> 16;
+  return ((unsigned)p - q * (unsigned)C) * NT + q;
+}
+__device__ __forceinline__ unsigned slot_div(int C) { return (65536u + (unsigned)C - 1u) / (unsigned)C; }
+
+// Where the radius of position p sits in LDS: the lanes of a wave own
+// positions C apart, which for even C would meet in a few banks (at C = 8
+// sixteen lanes in one); the block of eight is kept, so the index stays
+// inside the array.
+__device__ __forceinline__ unsigned rx(int p) { return (unsigned)p ^ (((unsigned)p >> 5) & 7u); }
 
 // Bitonic sort of the keys (kr, ki) of n positions in place (n <= NMAX),
 // padded with +inf keys to the next power of two.
 __device__ void bitonic_ions(double* kr, uint16_t* ki, int n) {
   int P = 1;
   while (P < n) P <<= 1;
-  for (int i = n + (int)threadIdx.x; i < P; i += NT) { kr[i] = INFINITY; ki[i] = 0xFFFF; }
+  for (int i = n + (int)threadIdx.x; i < P; i += NT) { kr[rx(i)] = INFINITY; ki[i] = 0xFFFF; }
   __syncthreads();
   for (int k = 2; k <= P; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
       for (int i = threadIdx.x; i < P; i += NT) {
         const int l = i ^ j;
         if (l > i) {
-          const double a = kr[i], b = kr[l];
+          const double a = kr[rx(i)], b = kr[rx(l)];
           const uint16_t ia = ki[i], ib = ki[l];
           const bool up = (i & k) == 0;
           const bool sw = up ? key_lt(b, (int32_t)ib, a, (int32_t)ia) : key_lt(a, (int32_t)ia, b, (int32_t)ib);
-          if (sw) { kr[i] = b; kr[l] = a; ki[i] = ib; ki[l] = ia; }
+          if (sw) { kr[rx(i)] = b; kr[rx(l)] = a; ki[i] = ib; ki[l] = ia; }
         }
       }
       __syncthreads();
@@ -150,7 +130,7 @@ __device__ __forceinline__ void ik_load(const double* kr, const uint16_t* ki, in
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
-    r[j] = p < n ? kr[p] : INFINITY;
+    r[j] = p < n ? kr[rx(p)] : INFINITY;
     k[j] = p < n ? (uint32_t)ki[p] : 0xffffffffu;
   }
 }
@@ -160,7 +140,7 @@ __device__ __forceinline__ void ik_store(double* kr, uint16_t* ki, int b0, int n
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
-    if (p < n) { kr[p] = r[j]; ki[p] = (uint16_t)k[j]; }
+    if (p < n) { kr[rx(p)] = r[j]; ki[p] = (uint16_t)k[j]; }
   }
 }
 // whether the wave's 256 keys are in order
@@ -287,48 +267,65 @@ __device__ void ions_fix_order(double* kr, uint16_t* ki, int n) {
     __syncthreads();
     bool out = false;
     const int q = 128 + 256 * lane;
-    if (q < n) out = ik_lt(kr[q], ki[q], kr[q - 1], ki[q - 1]);
+    if (q < n) out = ik_lt(kr[rx(q)], ki[q], kr[rx(q - 1)], ki[q - 1]);
     if (!__syncthreads_or(out)) return;     // also: every wave has read its junction keys
   }
   bitonic_ions(kr, ki, n);
 }
 
-// The interval of radius r among the nodes of species o (node 0 the axis,
-// node j = its ring j-1, node N+1 its edge): the lower node is j = cnt, the
-// number of its rings below r; t the fraction of the way to node j+1.
-// Returns false beyond the edge.
-struct Interval {
-  int j;
-  double t;
-};
-__device__ __forceinline__ bool interval_of(const double* ro, int N, double edge, double r, int cnt,
-                                            Interval& iv) {
-  iv.j = cnt;
-  const double rl = cnt == 0 ? 0.0 : ro[cnt - 1];
-  double rh;
-  if (cnt < N) {
-    rh = ro[cnt];
-  } else {
-    if (r > edge) { iv.t = 0.0; return false; }
-    rh = edge;
-  }
-  iv.t = (r - rl) / (rh - rl);
-  return true;
-}
-
-// ln rho of ring id at radius r as ln r0 + log1p((r - r0)/r0) (its rounding
-// scales with the ring's displacement, not with |ln rho|)
-__device__ __forceinline__ dd ring_log_id(const double* cst, int N, int id, double r) {
-  return dd_add_d({cst[IK_LNH * N + id], cst[IK_LNL * N + id]},
-                  log1p_fast((r - cst[IK_R0 * N + id]) * cst[IK_IR0 * N + id]));
-}
-
-// t of radius r in the node interval starting at node j of species o (the
-// same expression as interval_of)
+// The node interval of radius r of one species seen from the other (node 0
+// the axis, node j = its ring j-1, node N+1 its edge): the lower node is j =
+// the number of its rings below r; t the fraction of the way to node j+1,
+// exactly 1 at the upper node (the quotient's remainder is put back), so that
+// a ring at a node takes that node's value whole and the two species' sums
+// cancel at rest.
 __device__ __forceinline__ double interval_t(const double* ro, int N, double edge, double r, int j) {
-  const double rl = j == 0 ? 0.0 : ro[j - 1];
-  const double rh = j < N ? ro[j] : edge;
-  return (r - rl) / (rh - rl);
+  const double rl = j == 0 ? 0.0 : ro[rx(j - 1)];
+  const double rh = j < N ? ro[rx(j)] : edge;
+  const double d = rh - rl, n = r - rl;
+  const double id = rcp_nr(d);
+  const double t = n * id;
+  return __builtin_fma(__builtin_fma(-t, d, n), id, t);
+}
+
+// Number of the sorted radii ro[0..n) below r, the first lo of which are:
+// four at once (the answer for the next ring in order is a step or two
+// away), then galloping and bisection.
+__device__ __forceinline__ int rings_below(const double* ro, int lo, int n, double r) {
+  const int last = n - 1;
+  const double x0 = ro[rx(min(lo, last))], x1 = ro[rx(min(lo + 1, last))], x2 = ro[rx(min(lo + 2, last))],
+               x3 = ro[rx(min(lo + 3, last))];
+  const int c = (x0 < r ? 1 : 0) + (x1 < r ? 1 : 0) + (x2 < r ? 1 : 0) + (x3 < r ? 1 : 0);
+  int a = min(lo + c, n);
+  if (c < 4 || a == n) return a;
+  int b, step = 4;                       // ro[a - 1] < r
+  for (;;) {
+    b = a + step;
+    if (b > n) { b = n + 1; break; }
+    if (!(ro[rx(b - 1)] < r)) break;
+    a = b;
+    step <<= 1;
+  }
+  // the answer is in [a, b)
+  while (b - a > 1) {
+    const int m = (a + b) >> 1;
+    if (ro[rx(m - 1)] < r) a = m; else b = m;
+  }
+  return a;
+}
+
+// sums of two double-doubles, with one two_sum each
+struct DD2FastOp {
+  __device__ __forceinline__ Pack<4> operator()(const Pack<4>& a, const Pack<4>& b) const {
+    const dd x = dd_add_fast({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
+    const dd y = dd_add_fast({a.v[2], a.v[3]}, {b.v[2], b.v[3]});
+    return {{x.hi, x.lo, y.hi, y.lo}};
+  }
+};
+
+// a + t (b - a) of two double-doubles
+__device__ __forceinline__ dd dd_lerp(dd a, dd b, double t) {
+  return dd_add_fast(a, dd_mul_d(dd_add_fast(b, dd_neg(a)), t));
 }
 
 __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restrict__ insts) {
@@ -342,7 +339,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
 
   const int tid = threadIdx.x;
   const int N = I.N, C = I.C;
-  const size_t S = (size_t)C * NT;
+  const unsigned S = (unsigned)C * NT, div = slot_div(C);
   const int p0 = tid * C;
   const int cnt = N - p0 < 0 ? 0 : (N - p0 < C ? N - p0 : C);
   if (I.ctl[CTL_BREAK] >= 0) return;
@@ -350,9 +347,12 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
   const int end = I.first + I.count;
   const int n_an = I.n_an;
   const double dxi = I.dxi;
-  const double* const cst = I.cst;
   const double m_ion = I.m_i;
   const bool has_laser = I.has_laser != 0;   // else |a|^2 and its gradient are 0 (not stored)
+  const GA<D2> K = uview(reinterpret_cast<const D2*>(I.cst));
+  const GA<D2> W = uview(reinterpret_cast<const D2*>(I.work));
+  const GA<double> Wh = uview(reinterpret_cast<const double*>(I.work));   // its halves
+  const GA<int32_t> ORD = uview(I.ord), SID = uview(I.sid), JX = uview(I.jx);
   unsigned long long fixups = 0;
   int n = I.first;
   for (; n < end; ++n) {
@@ -378,131 +378,126 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     const int bm = I.nb ? I.boff[n + 1] - bt0 : 0;
     const bool b_lds = bm <= WAKE_BCAP;
     if (b_lds)
-      for (int i = tid; i < bm; i += NT) s_br[i] = I.br[bt0 + i];
-    const double* const stc = I.st[cur];
-    double* const stn = I.st[cur ^ 1];
+      for (int i = tid; i < bm; i += NT) s_br[i] = gptr(I.br)[bt0 + i];
+    const GA<D2> Sc = uview(reinterpret_cast<const D2*>(I.st[cur]));
+    const GA<D2> Sn = uview(reinterpret_cast<const D2*>(I.st[cur ^ 1]));
 
     // ---- order of each species ----
     int bad_order = 0;
     #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
-      const double* rho_s = stc + (size_t)(s * IS_N + IS_RHO) * N;
-      int32_t* const ord = I.ord + (size_t)s * N;
       double* const sr = s_r + s * NMAX;
-      #pragma unroll 4
+      const unsigned so = s * S, st = (unsigned)(s * IS_N + IS_RU) * S;
+      int dis = 0, pi = -1;
+      double pr = -INFINITY;
+      #pragma unroll 2
       for (int k = 0; k < cnt; ++k) {
         const int p = p0 + k;
-        const int id = ord[p];
-        sr[p] = rho_s[id];
+        const unsigned sl = so + k * NT + tid;
+        const int id = ORD[sl];
+        const unsigned hs = pslot(id, C, div);
+        const double r = Sc[st + hs].x;
+        SID.st(sl, (int32_t)hs);
+        sr[rx(p)] = r;
         s_id[p] = (uint16_t)id;
+        if (!key_lt(pr, pi, r, id)) dis = 1;
+        pr = r;
+        pi = id;
       }
       __syncthreads();
-      int dis = 0;
-      #pragma unroll 1
-      for (int k = 0; k < cnt; ++k) {
-        const int p = p0 + k;
-        if (p > 0 && !key_lt(sr[p - 1], (int32_t)s_id[p - 1], sr[p], (int32_t)s_id[p])) dis = 1;
-      }
-      const bool resort = __syncthreads_or(dis) != 0;
-      if (resort) {
+      if (cnt > 0 && p0 > 0 && !key_lt(sr[rx(p0 - 1)], (int32_t)s_id[p0 - 1], sr[rx(p0)], (int32_t)s_id[p0])) dis = 1;
+      if (__syncthreads_or(dis)) {
         ions_fix_order(sr, s_id, N);
         ++fixups;
+        #pragma unroll 2
+        for (int k = 0; k < cnt; ++k) {
+          const unsigned sl = so + k * NT + tid;
+          int id = s_id[p0 + k];
+          // a padding key among the first N positions: a radius that is not a
+          // finite number (state injected from device memory) -- stop there
+          if (id >= N) { id = 0; bad_order = 1; }
+          ORD.st(sl, id);
+          SID.st(sl, (int32_t)pslot(id, C, div));
+        }
       }
-      int32_t* const sid = I.sid + (size_t)s * S;
-      double* const wk = I.work + (size_t)s * IW_N * S;
-      const double* const st_s = stc + (size_t)s * IS_N * N;
-      // the ring's weights and momentum into the slots of its position (used
-      // by most phases; the rest is read through the ring id where needed)
-      #pragma unroll 4
-      for (int k = 0; k < cnt; ++k) {
-        const int p = p0 + k;
-        const unsigned sl = k * NT + tid;
-        int id = s_id[p];
-        // a padding key among the first N positions: a radius that is not a
-        // finite number (state injected from device memory) -- stop there
-        if (id >= N) { id = 0; bad_order = 1; }
-        sid[sl] = id;
-        if (resort) ord[p] = id;
-        wk[IW_W * S + sl] = cst[IK_W * N + id];
-        wk[IW_WH * S + sl] = cst[IK_WH * N + id];
-        wk[IW_U * S + sl] = st_s[IS_U * N + id];
-      }
-      __syncthreads();              // s_id is the next species' too
     }
 
-    // ---- own sums: psi and d_rho psi of each species at its rings ----
+    // ---- own sums: ln rho, chunk sums of w and w ln rho ----
     dd sw[2], swl[2];
+    #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const double* const wk = I.work + (size_t)s * IW_N * S;
-      const int32_t* const sid = I.sid + (size_t)s * S;
-      const double* sr = s_r + s * NMAX;
+      const unsigned wo = (unsigned)(s * IW_N) * S;
+      const double* const sr = s_r + s * NMAX;
       sw[s] = dd_make(0.0);
       swl[s] = dd_make(0.0);
       #pragma unroll 2
       for (int k = 0; k < cnt; ++k) {
         const unsigned sl = k * NT + tid;
-        const double r = sr[p0 + k];
-        const double w = wk[IW_W * S + sl];
-        const dd lnr = ring_log_id(cst, N, sid[sl], r);
-        sw[s] = dd_add_d(sw[s], w);
-        swl[s] = dd_add(swl[s], dd_mul_d(lnr, w));
+        const unsigned hs = (unsigned)SID[s * S + sl];
+        const D2 w = K[IK_W * S + hs], r0 = K[IK_R0 * S + hs], l0 = K[IK_LN * S + hs];
+        const double r = sr[rx(p0 + k)];
+        // ln rho as ln r0 + log1p((r - r0)/r0): its rounding scales with the
+        // ring's displacement, not with |ln rho|
+        const dd lnr = dd_add_d({l0.x, l0.y}, log1p_fast((r - r0.x) * r0.y));
+        W.st(wo + IW_W * S + sl, w);
+        W.st(wo + IW_LN * S + sl, d2(lnr.hi, lnr.lo));
+        sw[s] = dd_add_d(sw[s], w.x);
+        swl[s] = dd_add_fast(swl[s], dd_mul_d(lnr, w.x));
       }
     }
     Pack<4> exP, totP, exS, totS;
-    block_prefix_suffix<NT, 4, 4, DD2Op, DD2Op, true>(
-        Pack<4>{{sw[0].hi, sw[0].lo, sw[1].hi, sw[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2Op(),
-        Pack<4>{{swl[0].hi, swl[0].lo, swl[1].hi, swl[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2Op(),
+    block_prefix_suffix<NT, 4, 4, DD2FastOp, DD2FastOp, true>(
+        Pack<4>{{sw[0].hi, sw[0].lo, sw[1].hi, sw[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(),
+        Pack<4>{{swl[0].hi, swl[0].lo, swl[1].hi, swl[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(),
         s_scan, exP, totP, exS, totS);
+    // node tables: psi and d_rho psi of each species at its own rings
     #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
-      const double q = s ? 1.0 : -1.0;
-      const double* const wk = I.work + (size_t)s * IW_N * S;
-      const int32_t* const sid = I.sid + (size_t)s * S;
-      double* const tb = I.tab + (size_t)s * IT_N * S;
+      const bool neg = s == 1;              // psi = -q (...): the electrons' q is -1
+      const unsigned wo = (unsigned)(s * IW_N) * S;
       double* const sc = s_sc + SC_N * s;
       const double* sr = s_r + s * NMAX;
       const dd Q = s ? dd{totP.v[2], totP.v[3]} : dd{totP.v[0], totP.v[1]};
       dd below = s ? dd{exP.v[2], exP.v[3]} : dd{exP.v[0], exP.v[1]};
       // sum over positions >= p
-      dd rest = dd_add(s ? dd{exS.v[2], exS.v[3]} : dd{exS.v[0], exS.v[1]}, s ? swl[1] : swl[0]);
-      #pragma unroll 1
+      dd rest = dd_add_fast(s ? dd{exS.v[2], exS.v[3]} : dd{exS.v[0], exS.v[1]}, s ? swl[1] : swl[0]);
+      #pragma unroll 2
       for (int k = 0; k < cnt; ++k) {
         const unsigned sl = k * NT + tid;
-        const int p = p0 + k;
-        const double r = sr[p];
-        const double w = wk[IW_W * S + sl], wh = wk[IW_WH * S + sl];
-        const int id = sid[sl];
-        const dd lnr = ring_log_id(cst, N, id, r);
-        const dd above = dd_sub(rest, dd_mul_d(lnr, w));
+        const D2 w = W[wo + IW_W * S + sl], l = W[wo + IW_LN * S + sl];
+        const dd lnr = {l.x, l.y};
+        const double r = sr[rx(p0 + k)];
+        rest = dd_add_fast(rest, dd_neg(dd_mul_d(lnr, w.x)));     // sum over positions > p
         // psi = -q ((sum_{k<i} w_k + w_i) ln rho_i + sum_{k>i} w_k ln rho_k)
-        dd ps = dd_add(dd_mul(dd_add_d(below, w), lnr), above);
         // d_rho psi = -q (sum_{k<i} w_k + w^_i) / rho_i
-        dd dp = dd_div_d(dd_add_d(below, wh), r);
-        if (q > 0.0) { ps = dd_neg(ps); dp = dd_neg(dp); }
-        tb[IT_PSH * S + sl] = ps.hi;
-        tb[IT_PSL * S + sl] = ps.lo;
-        tb[IT_DPH * S + sl] = dp.hi;
-        tb[IT_DPL * S + sl] = dp.lo;
-        below = dd_add_d(below, w);
-        rest = above;
-        if (p == N - 1) {
-          // outer edge: the outermost ring plus half its initial extent, and
-          // the exterior field there (-q Q ln r, -q Q / r)
-          const double edge = r + cst[IK_DR * N + id] / 2.0;
-          const dd lne = dd_add_d(lnr, log1p_fast((edge - r) / r));
-          dd eps = dd_mul(Q, lne);
-          dd edp = dd_div_d(Q, edge);
-          if (q > 0.0) { eps = dd_neg(eps); edp = dd_neg(edp); }
-          sc[SC_EDGE] = edge;
-          sc[SC_EPH] = eps.hi;
-          sc[SC_EPL] = eps.lo;
-          sc[SC_EDP] = edp.hi;
-          sc[SC_EDL] = edp.lo;
-        }
+        const dd Sn_ = dd_add_d(below, w.x);
+        dd ps = dd_add_fast(dd_mul(Sn_, lnr), rest);
+        dd dp = dd_div_rcp(dd_add_d(below, w.y), r, rcp_nr(r));
+        below = Sn_;
+        if (neg) { ps = dd_neg(ps); dp = dd_neg(dp); }
+        W.st(wo + IW_T0 * S + sl, d2(ps.hi, ps.lo));
+        W.st(wo + IW_T1 * S + sl, d2(dp.hi, dp.lo));
+      }
+      if (cnt > 0 && p0 + cnt == N) {
+        // outer edge: the outermost ring plus half its initial extent, and
+        // the exterior field there (-q Q ln r, -q Q / r)
+        const unsigned sl = (cnt - 1) * NT + tid;
+        const D2 l = W[wo + IW_LN * S + sl];
+        const double r = sr[rx(N - 1)];
+        const double edge = r + gptr(I.cst)[2 * IK_DR * S + (unsigned)SID[s * S + sl]] / 2.0;
+        const dd lne = dd_add_d({l.x, l.y}, log1p_fast((edge - r) / r));
+        dd eps = dd_mul(Q, lne);
+        dd edp = dd_div_d(Q, edge);
+        if (neg) { eps = dd_neg(eps); edp = dd_neg(edp); }
+        sc[SC_EDGE] = edge;
+        sc[SC_EPH] = eps.hi;
+        sc[SC_EPL] = eps.lo;
+        sc[SC_EDP] = edp.hi;
+        sc[SC_EDL] = edp.lo;
       }
       if (tid == 0) {
         dd pa = s ? dd{totS.v[2], totS.v[3]} : dd{totS.v[0], totS.v[1]};
-        if (q > 0.0) pa = dd_neg(pa);
+        if (neg) pa = dd_neg(pa);
         sc[SC_PAH] = pa.hi;
         sc[SC_PAL] = pa.lo;
         sc[SC_QH] = Q.hi;
@@ -511,74 +506,71 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     }
     __syncthreads();
 
-    // ---- gather psi, d_rho psi; local quantities, sources; d_zeta psi sums ----
+    // ---- gather psi, d_rho psi; sources; d_zeta psi sums ----
     int bad = bad_order;
-    const double* const br = b_lds ? s_br : I.br + bt0;
-    const double* const bcq = I.bcum + bt0;
+    const WAKE_GLOBAL double* const brg = gptr(I.br) + bt0;
+    const WAKE_GLOBAL double* const bcq = gptr(I.bcum) + bt0;
     dd szc0 = dd_make(0.0), szc1 = dd_make(0.0);
     #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
       const int o = s ^ 1;
       const double q = s ? 1.0 : -1.0, m = s ? m_ion : 1.0;
-      const double qm = q / m, qq2 = (q * q) / (2.0 * m * m);
-      const double qo = o ? 1.0 : -1.0;
-      double* const wk = I.work + (size_t)s * IW_N * S;
-      const int32_t* const sid = I.sid + (size_t)s * S;
-      const double* tb = I.tab + (size_t)s * IT_N * S;
-      const double* tbo = I.tab + (size_t)o * IT_N * S;
-      int32_t* const jx = I.jx + (size_t)s * S;
+      const double qm = q / m;
+      const unsigned wo = (unsigned)(s * IW_N) * S, wx = (unsigned)(o * IW_N) * S;
       const double* sr = s_r + s * NMAX;
       const double* ro = s_r + o * NMAX;
       const double* sco = s_sc + SC_N * o;
       const double edge_o = sco[SC_EDGE];
-      const dd Qo = {sco[SC_QH], sco[SC_QL]};
       dd szc = dd_make(0.0);
       int lo = 0, blo = 0;
       #pragma unroll 1
       for (int k = 0; k < cnt; ++k) {
         const unsigned sl = k * NT + tid;
-        const double r = sr[p0 + k];
-        const double u = wk[IW_U * S + sl];
-        const double w = wk[IW_W * S + sl];
-        lo = count_below(ro, lo, N, r, k > 0);
-        Interval iv;
+        const unsigned hs = (unsigned)SID[s * S + sl];
+        const double r = sr[rx(p0 + k)];
+        if (k == 0) {
+          int a = 0, b = N;
+          while (a < b) {
+            const int c = (a + b) >> 1;
+            if (ro[rx(c)] < r) a = c + 1; else b = c;
+          }
+          lo = a;
+        } else {
+          lo = rings_below(ro, lo, N, r);
+        }
+        // both tables' nodes (clamped; the end nodes put in below)
+        const unsigned u0 = pslot(max(lo - 1, 0), C, div), u1 = pslot(min(lo, N - 1), C, div);
+        const D2 a0 = W[wx + IW_T0 * S + u0], a1 = W[wx + IW_T1 * S + u0];
+        const D2 b0 = W[wx + IW_T0 * S + u1], b1 = W[wx + IW_T1 * S + u1];
+        const D2 t0 = W[wo + IW_T0 * S + sl], t1 = W[wo + IW_T1 * S + sl];
+        const double w = W[wo + IW_W * S + sl].x;
+        const double u = Sc[(unsigned)(s * IS_N + IS_RU) * S + hs].y;
         dd pg, dg;
-        if (interval_of(ro, N, edge_o, r, lo, iv)) {
+        if (lo < N || !(r > edge_o)) {
           // both in double-double: at a ring of the other species (t = 0 or
           // 1) its node value is taken whole, so the two species' sums
           // cancel there as exactly as they do at rest
-          dd pl, ph, dl, dh;
-          if (iv.j == 0) {
-            pl = {sco[SC_PAH], sco[SC_PAL]};
-            dl = dd_make(0.0);
-          } else {
-            const unsigned u0 = pslot(iv.j - 1, C);
-            pl = {tbo[IT_PSH * S + u0], tbo[IT_PSL * S + u0]};
-            dl = {tbo[IT_DPH * S + u0], tbo[IT_DPL * S + u0]};
-          }
-          if (iv.j < N) {
-            const unsigned u1 = pslot(iv.j, C);
-            ph = {tbo[IT_PSH * S + u1], tbo[IT_PSL * S + u1]};
-            dh = {tbo[IT_DPH * S + u1], tbo[IT_DPL * S + u1]};
-          } else {
-            ph = {sco[SC_EPH], sco[SC_EPL]};
-            dh = {sco[SC_EDP], sco[SC_EDL]};
-          }
-          pg = dd_add(pl, dd_mul_d(dd_sub(ph, pl), iv.t));
-          dg = dd_add(dl, dd_mul_d(dd_sub(dh, dl), iv.t));
-          jx[sl] = iv.j;
+          dd pl = {a0.x, a0.y}, dl = {a1.x, a1.y}, ph = {b0.x, b0.y}, dh = {b1.x, b1.y};
+          if (lo == 0) { pl = {sco[SC_PAH], sco[SC_PAL]}; dl = dd_make(0.0); }
+          if (lo == N) { ph = {sco[SC_EPH], sco[SC_EPL]}; dh = {sco[SC_EDP], sco[SC_EDL]}; }
+          const double t = interval_t(ro, N, edge_o, r, lo);
+          pg = dd_lerp(pl, ph, t);
+          dg = dd_lerp(dl, dh, t);
+          JX.st(s * S + sl, lo);
         } else {                  // beyond the other species' edge: its exterior field
-          pg = dd_mul(Qo, ring_log_id(cst, N, sid[sl], r));
+          const dd Qo = {sco[SC_QH], sco[SC_QL]};
+          const D2 l = W[wo + IW_LN * S + sl];
+          pg = dd_mul(Qo, {l.x, l.y});
           dg = dd_div_d(Qo, r);
-          if (qo > 0.0) { pg = dd_neg(pg); dg = dd_neg(dg); }
-          jx[sl] = -1;
+          if (o) { pg = dd_neg(pg); dg = dd_neg(dg); }
+          JX.st(s * S + sl, -1);
         }
-        const double psi = dd_round(dd_add(pg, {tb[IT_PSH * S + sl], tb[IT_PSL * S + sl]}));
-        const double dpsi = dd_round(dd_add(dg, {tb[IT_DPH * S + sl], tb[IT_DPL * S + sl]}));
+        const double psi = dd_round(dd_add_fast(pg, {t0.x, t0.y}));
+        const double dpsi = dd_round(dd_add_fast(dg, {t1.x, t1.y}));
         // beam charge inside r (table entries strictly below), analytic beams, lasers
         double lam = 0.0;
         if (bm > 0) {
-          blo = count_below(br, blo, bm, r, k > 0);
+          blo = b_lds ? count_below(s_br, blo, bm, r, k > 0) : count_below(brg, blo, bm, r, k > 0);
           if (blo > 0) lam = bcq[blo - 1];
         }
         double a2 = 0.0, da2 = 0.0;
@@ -595,39 +587,32 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
         }
         const double pb = 1.0 - qm * psi;
         if (!(pb > 0.0) || !isfinite(pb)) bad = 1;
-        const double c = q * u / (r * pb);
+        const double ir = rcp_nr(r);
+        const double c = q * u * (ir * rcp_nr(pb));
         szc = dd_add_d(szc, w * c);
-        wk[IW_PSI * S + sl] = psi;
-        wk[IW_DPSI * S + sl] = dpsi;
-        wk[IW_PB * S + sl] = pb;
-        wk[IW_BB * S + sl] = lam / r;
-        if (has_laser) {
-          wk[IW_A2 * S + sl] = a2;
-          wk[IW_DA2 * S + sl] = da2;
-        }
+        W.st(wo + IW_F * S + sl, d2(psi, dpsi));
+        W.st(wo + IW_UC * S + sl, d2(u, c));
+        Wh.st(2 * (wo + IW_BB * S + sl), lam * ir);
+        if (has_laser) W.st(wo + IW_A2 * S + sl, d2(a2, da2));
       }
       if (s) szc1 = szc; else szc0 = szc;
     }
     Pack<4> dzs, dzt;
     dzs = block_suffix<NT, 4>(Pack<4>{{szc0.hi, szc0.lo, szc1.hi, szc1.lo}},
-                              Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2Op(), s_scan, dzt);
+                              Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(), s_scan, dzt);
     // own d_zeta psi at each ring: the rings outside with w, the ring itself
     // with w - w^
-    #pragma unroll 1
+    #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const double q = s ? 1.0 : -1.0;
-      const double* wk = I.work + (size_t)s * IW_N * S;
-      double* const tb = I.tab + (size_t)s * IT_N * S;
-      const double* sr = s_r + s * NMAX;
+      const unsigned wo = (unsigned)(s * IW_N) * S;
       dd above = s ? dd{dzs.v[2], dzs.v[3]} : dd{dzs.v[0], dzs.v[1]};
-      #pragma unroll 1
+      #pragma unroll 2
       for (int k = cnt - 1; k >= 0; --k) {
         const unsigned sl = k * NT + tid;
-        const double r = sr[p0 + k];
-        const double w = wk[IW_W * S + sl], wh = wk[IW_WH * S + sl];
-        const double c = q * wk[IW_U * S + sl] / (r * wk[IW_PB * S + sl]);
-        tb[IT_DZ * S + sl] = dd_round(dd_add_d(above, (w - wh) * c));
-        above = dd_add_d(above, w * c);
+        const D2 w = W[wo + IW_W * S + sl];
+        const double c = W[wo + IW_UC * S + sl].y;
+        Wh.st(2 * (wo + IW_ZB * S + sl), dd_round(dd_add_d(above, (w.x - w.y) * c)));
+        above = dd_add_d(above, w.x * c);
       }
       if (tid == 0) {
         s_sc[SC_N * s + SC_DZH] = s ? dzt.v[2] : dzt.v[0];
@@ -636,206 +621,170 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     }
     __syncthreads();
 
-    // ---- gather d_zeta psi; electrons: coefficients and chunk transfer ----
+    // ---- electrons: the ions' d_zeta psi; offsets, chunk transfer and lambda ----
+    const unsigned wi = (unsigned)IW_N * S;      // the ions' planes (the electrons' start at 0)
+    const double* const sre = s_r;
+    const double* const sri = s_r + NMAX;
     Pack<4> G = mat_ident();
-    #pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
-      const int o = s ^ 1;
-      double* const wk = I.work + (size_t)s * IW_N * S;
-      const double* tb = I.tab + (size_t)s * IT_N * S;
-      const double* tbo = I.tab + (size_t)o * IT_N * S;
-      const int32_t* jx = I.jx + (size_t)s * S;
-      const double* sr = s_r + s * NMAX;
-      const double* ro = s_r + o * NMAX;
-      const double edge_o = s_sc[SC_N * o + SC_EDGE];
-      const double dza_o = dd_round({s_sc[SC_N * o + SC_DZH], s_sc[SC_N * o + SC_DZL]});
+    double la = 0.0, lb = 0.0;
+    {
+      const double edge_i = s_sc[SC_N + SC_EDGE];
+      const double dza_i = dd_round({s_sc[SC_N + SC_DZH], s_sc[SC_N + SC_DZL]});
       #pragma unroll 1
       for (int k = 0; k < cnt; ++k) {
         const unsigned sl = k * NT + tid;
-        const int j = jx[sl];
-        double dz = tb[IT_DZ * S + sl];
+        const int j = JX[sl];
+        const D2 w = W[IW_W * S + sl], f = W[IW_F * S + sl];
+        const double u = W[IW_UC * S + sl].x;
+        const double bb = Wh[2 * (IW_BB * S + sl)];
+        double dz = Wh[2 * (IW_ZB * S + sl)];
+        const double r = sre[rx(p0 + k)];
         if (j >= 0) {
-          const double t = interval_t(ro, N, edge_o, sr[p0 + k], j);
-          const double dl = j == 0 ? dza_o : tbo[IT_DZ * S + pslot(j - 1, C)];
-          const double dh = j < N ? tbo[IT_DZ * S + pslot(j, C)] : 0.0;
+          const double dlo = Wh[2 * (wi + IW_ZB * S + pslot(max(j - 1, 0), C, div))];
+          const double dhi = Wh[2 * (wi + IW_ZB * S + pslot(min(j, N - 1), C, div))];
+          const double t = interval_t(sri, N, edge_i, r, j);
+          const double dl = j == 0 ? dza_i : dlo, dh = j < N ? dhi : 0.0;
           dz += (1.0 - t) * dl + t * dh;
         }
-        wk[IW_DZ * S + sl] = dz;
-        if (s == 0) {
-          const double r = sr[p0 + k];
-          const double w = wk[IW_W * S + sl];
-          const double irho = rcp_nr(r);
-          const double a2 = has_laser ? wk[IW_A2 * S + sl] : 0.0;
-          const double da2 = has_laser ? wk[IW_DA2 * S + sl] : 0.0;
-          const IonsLocal L = ions_local(irho, wk[IW_U * S + sl], w, wk[IW_PSI * S + sl], a2);
-          double B, Cc, sa, sb;
-          ring_BC(irho, wk[IW_U * S + sl], w, L, wk[IW_DPSI * S + sl], dz, wk[IW_BB * S + sl], da2, B,
-                  Cc);
-          rec_offset(L.A, B, Cc, r, sa, sb);
-          G = mat_mul(rec_matrix(L.A, r, irho), G);
-          wk[IW_A * S + sl] = L.A;
-          wk[IW_C * S + sl] = Cc;
-          wk[IW_SA * S + sl] = sa;
-          wk[IW_SB * S + sl] = sb;
-        }
+        D2 a2 = d2(0.0, 0.0);
+        if (has_laser) a2 = W[IW_A2 * S + sl];
+        const double ir = rcp_nr(r);
+        const Local L = local_of(ir, u, w.x, f.x, a2.x);
+        double cc, sa;
+        ring_source(ir, u, w.x, L, a2.x, f.y, dz, bb, a2.y, cc, sa);
+        const double r2 = r * r, hAi = 0.5 * L.A * ir, rC = 0.5 * w.x * cc;
+        const double m0 = __builtin_fma(r2, G.v[0], G.v[2]), m1 = __builtin_fma(r2, G.v[1], G.v[3]);
+        const double y0 = hAi * m0, y1 = hAi * m1;
+        G.v[0] += y0;
+        G.v[1] += y1;
+        G.v[2] = __builtin_fma(-r2, y0, G.v[2]);
+        G.v[3] = __builtin_fma(-r2, y1, G.v[3]);
+        la = __builtin_fma(-sa, m0, __builtin_fma(G.v[0], rC, la));
+        lb = __builtin_fma(-sa, m1, __builtin_fma(G.v[1], rC, lb));
+        W.st(IW_E * S + sl, d2(L.A, sa));
+        W.st(IW_DC * S + sl, d2(dz, cc));
       }
     }
     // growing mode at the chunk start, decaying mode at the chunk end
     Pack<4> gp, gt, hx, ht;
     block_prefix_suffix<NT, 4, 4, FwdMatOp, BwdMatOp, true>(
         G, mat_ident(), FwdMatOp(), mat_adj(G), mat_ident(), BwdMatOp(), s_scan, gp, gt, hx, ht);
-    const double W = gt.v[0];                 // det[g_N, (0, 1)]
-    const double iW = 1.0 / W;
-    double* const wke = I.work;
-    const double* sre = s_r;
-    // g_i and the det-sums of the chunk (E forward, D backward)
-    double Ec = 0.0, Dc = 0.0;
-    {
-      double ga = gp.v[0], gb = gp.v[2];
-      #pragma unroll 1
-      for (int k = 0; k < cnt; ++k) {
-        const unsigned sl = k * NT + tid;
-        const double r = sre[p0 + k];
-        wke[IW_GA * S + sl] = ga;
-        wke[IW_GB * S + sl] = gb;
-        wke[IW_E * S + sl] = Ec;
-        const Pack<4> M = rec_matrix(wke[IW_A * S + sl], r, rcp_nr(r));
-        const double na = M.v[0] * ga + M.v[1] * gb, nb = M.v[2] * ga + M.v[3] * gb;
-        ga = na;
-        gb = nb;
-        Ec += ga * wke[IW_SB * S + sl] - gb * wke[IW_SA * S + sl];
-      }
-      double ha = hx.v[1], hb = hx.v[3];
-      #pragma unroll 1
-      for (int k = cnt - 1; k >= 0; --k) {
-        const unsigned sl = k * NT + tid;
-        const double r = sre[p0 + k];
-        Dc += wke[IW_SA * S + sl] * hb - wke[IW_SB * S + sl] * ha;
-        const Pack<4> Mi = mat_adj(rec_matrix(wke[IW_A * S + sl], r, rcp_nr(r)));
-        const double na = Mi.v[0] * ha + Mi.v[1] * hb, nb = Mi.v[2] * ha + Mi.v[3] * hb;
-        ha = na;
-        hb = nb;
-      }
-    }
+    const double W_ = gt.v[0];                // det[g_N, (0, 1)]
+    const double iW = 1.0 / W_;
+    const double gsa = gp.v[0], gsb = gp.v[2], hea = hx.v[1], heb = hx.v[3];
+    // the chunk's sums of det[g_i, s_i] and det[s_i, h_i]
+    const double le = gsa * la + gsb * lb;
+    const double ld = -((G.v[3] * hea - G.v[1] * heb) * la + (G.v[0] * heb - G.v[2] * hea) * lb);
     Pack<1> ep, et, dsf, dt;
-    block_prefix_suffix<NT, 1, 1, SumOp<1>, SumOp<1>, true>(Pack<1>{{Ec}}, Pack<1>{{0.0}}, SumOp<1>(),
-                                                           Pack<1>{{Dc}}, Pack<1>{{0.0}}, SumOp<1>(),
+    block_prefix_suffix<NT, 1, 1, SumOp<1>, SumOp<1>, true>(Pack<1>{{le}}, Pack<1>{{0.0}}, SumOp<1>(),
+                                                           Pack<1>{{ld}}, Pack<1>{{0.0}}, SumOp<1>(),
                                                            s_scan, ep, et, dsf, dt);
     const double bN = et.v[0] * iW;           // b_N = E_N / W (a_N = 0)
-    {
-      // x_{i-1} = (h_{i-1} E_{i-1} - g_{i-1} D_{i-1}) / W and B^(p) at ring i
-      double* const tbe = I.tab;
-      double ha = hx.v[1], hb = hx.v[3];
-      double D = dsf.v[0];
-      #pragma unroll 1
-      for (int k = cnt - 1; k >= 0; --k) {
-        const unsigned sl = k * NT + tid;
-        const double r = sre[p0 + k];
-        const double irho = rcp_nr(r);
-        D += wke[IW_SA * S + sl] * hb - wke[IW_SB * S + sl] * ha;
-        const Pack<4> Mi = mat_adj(rec_matrix(wke[IW_A * S + sl], r, irho));
-        const double na = Mi.v[0] * ha + Mi.v[1] * hb, nb = Mi.v[2] * ha + Mi.v[3] * hb;
-        ha = na;
-        hb = nb;
-        const double E = ep.v[0] + wke[IW_E * S + sl];
-        const double ga = wke[IW_GA * S + sl], gb = wke[IW_GB * S + sl];
-        const double a = (ha * E - ga * D) * iW;
-        const double b = (hb * E - gb * D) * iW;
-        const double w = wke[IW_W * S + sl], wh = wke[IW_WH * S + sl];
-        const double bp = a * r + b * irho + (wh / w) * wke[IW_C * S + sl];
-        tbe[IT_BP * S + sl] = bp;
-        wke[IW_BT * S + sl] = wke[IW_BB * S + sl] + bp;
-      }
-    }
-    __syncthreads();
 
-    // ---- ions: B^(p) interpolated between the electron rings ----
-    {
-      double* const wki = I.work + (size_t)IW_N * S;
-      const int32_t* jxi = I.jx + S;
-      const double* tbe = I.tab;
-      const double edge_e = s_sc[SC_EDGE];
-      const double* sri = s_r + NMAX;
-      #pragma unroll 1
-      for (int k = 0; k < cnt; ++k) {
-        const unsigned sl = k * NT + tid;
-        const int j = jxi[sl];
-        double bp;
-        if (j >= 0) {
-          const double t = interval_t(s_r, N, edge_e, sri[p0 + k], j);
-          const double bl = j == 0 ? 0.0 : tbe[IT_BP * S + pslot(j - 1, C)];
-          const double bh = j < N ? tbe[IT_BP * S + pslot(j, C)] : bN / edge_e;
-          bp = (1.0 - t) * bl + t * bh;
-        } else {
-          bp = bN / sri[p0 + k];
-        }
-        wki[IW_BT * S + sl] = wki[IW_BB * S + sl] + bp;
-      }
-    }
-
-    // ---- fields out, push ----
+    // ---- fields out, push: electrons (backward), then ions ----
     const bool do_push = n < I.n_xi - 1;
     const bool rec_snap = I.stride > 0 && (n % I.stride) == 0;
     const bool rec_last = n == end - 1;
-    #pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
+    auto finish = [&](int s, unsigned sl, unsigned hs, double r, double u, D2 f, double dz, double bt, D2 a2,
+                      D2 fp) {
       const double q = s ? 1.0 : -1.0, m = s ? m_ion : 1.0;
       const double qm = q / m, q24 = (q * q) / (4.0 * m * m), qq2 = (q * q) / (2.0 * m * m);
-      const double* frp = stc + (size_t)(s * IS_N + IS_FR) * N;
-      const double* fup = stc + (size_t)(s * IS_N + IS_FU) * N;
-      const int32_t* sid = I.sid + (size_t)s * S;
-      const double* wk = I.work + (size_t)s * IW_N * S;
-      const double* sr = s_r + s * NMAX;
-      double* const rn_s = stn + (size_t)(s * IS_N + IS_RHO) * N;
-      double* const un_s = stn + (size_t)(s * IS_N + IS_U) * N;
-      double* const fr_s = stn + (size_t)(s * IS_N + IS_FR) * N;
-      double* const fu_s = stn + (size_t)(s * IS_N + IS_FU) * N;
-      double* const snap = rec_snap ? I.snap[s] + (size_t)(n / I.stride) * OUT_N * N : nullptr;
-      double* const last = I.last[s];
+      const double psi = f.x, dpsi = f.y, ez = -dz;
+      if (!(isfinite(psi) && isfinite(dpsi) && isfinite(ez) && isfinite(bt))) bad = 1;
+      if (rec_snap || rec_last) {
+        const unsigned id = (hs & (NT - 1)) * (unsigned)C + hs / NT;      // the ring of home slot hs
+        if (rec_snap) {
+          WAKE_GLOBAL double* o = gptr(I.snap[s]) + (size_t)(n / I.stride) * OUT_N * N + id;
+          o[OUT_PSI * N] = psi; o[OUT_ERBT * N] = -dpsi; o[OUT_EZ * N] = ez; o[OUT_BT * N] = bt;
+          o[OUT_RHO * N] = r; o[OUT_UR * N] = u;
+        }
+        if (rec_last) {
+          WAKE_GLOBAL double* o = gptr(I.last[s]) + id;
+          o[OUT_PSI * N] = psi; o[OUT_ERBT * N] = -dpsi; o[OUT_EZ * N] = ez; o[OUT_BT * N] = bt;
+          o[OUT_RHO * N] = r; o[OUT_UR * N] = u;
+        }
+      }
+      if (do_push) {
+        const double pb = 1.0 - qm * psi, ipb = rcp_nr(pb);
+        const double gm = (1.0 + u * u + pb * pb + qq2 * a2.x) * (0.5 * ipb);   // eq. motion_4
+        const double f_r = u * ipb;
+        const double f_u = -(qm * (gm * dpsi * ipb - bt) + q24 * a2.y * ipb);
+        double pr = f_r, pu = f_u;
+        if (n > 0) { pr = fp.x; pu = fp.y; }
+        double rn = r + dxi * (1.5 * f_r - 0.5 * pr);
+        double un = u + dxi * (1.5 * f_u - 0.5 * pu);
+        double sr_ = f_r, su = f_u;
+        if (rn < 0.0) { rn = -rn; un = -un; sr_ = -sr_; su = -su; }
+        if (!(isfinite(rn) && isfinite(un))) bad = 1;
+        Sn.st((unsigned)(s * IS_N + IS_RU) * S + hs, d2(rn, un));
+        Sn.st((unsigned)(s * IS_N + IS_F) * S + hs, d2(sr_, su));
+      }
+    };
+    {
+      double ga = G.v[0] * gsa + G.v[1] * gsb, gb = G.v[2] * gsa + G.v[3] * gsb;   // at the chunk end
+      double ha = hea, hb = heb;
+      double E = ep.v[0] + le, D = dsf.v[0];
+      #pragma unroll 1
+      for (int k = cnt - 1; k >= 0; --k) {
+        const unsigned sl = k * NT + tid;
+        const unsigned hs = (unsigned)SID[sl];
+        const D2 w = W[IW_W * S + sl], f = W[IW_F * S + sl], As = W[IW_E * S + sl], dc = W[IW_DC * S + sl];
+        const double u = W[IW_UC * S + sl].x, bb = Wh[2 * (IW_BB * S + sl)];
+        D2 a2 = d2(0.0, 0.0);
+        if (has_laser) a2 = W[IW_A2 * S + sl];
+        const D2 fp = Sc[(unsigned)IS_F * S + hs];
+        const double r = sre[rx(p0 + k)];
+        const double ir = rcp_nr(r), r2 = r * r, hAi = 0.5 * As.x * ir, rC = 0.5 * w.x * dc.y;
+        const double mg = __builtin_fma(r2, ga, gb), mh = __builtin_fma(r2, ha, hb);
+        D = __builtin_fma(As.y, mh, __builtin_fma(-rC, ha, D));   // D_{i-1}
+        E = __builtin_fma(As.y, mg, __builtin_fma(-rC, ga, E));   // E_{i-1}
+        const double yg = hAi * mg, yh = hAi * mh;
+        ga -= yg;
+        gb = __builtin_fma(r2, yg, gb);
+        ha -= yh;
+        hb = __builtin_fma(r2, yh, hb);
+        // a_{i-1} rho + b_{i-1} / rho and the ring's own share w^ C / w
+        const double bp = ir * __builtin_fma(iW, __builtin_fma(E, mh, -(D * mg)), 0.5 * w.y * dc.y);
+        Wh.st(2 * (IW_ZB * S + sl) + 1, bp);
+        finish(0, sl, hs, r, u, f, dc.x, bb + bp, a2, fp);
+      }
+    }
+    __syncthreads();
+    {
+      const double edge_e = s_sc[SC_EDGE];
+      const double dza_e = dd_round({s_sc[SC_DZH], s_sc[SC_DZL]});
       #pragma unroll 1
       for (int k = 0; k < cnt; ++k) {
         const unsigned sl = k * NT + tid;
-        const int id = sid[sl];
-        const double r = sr[p0 + k];
-        const double u = wk[IW_U * S + sl], psi = wk[IW_PSI * S + sl], dpsi = wk[IW_DPSI * S + sl];
-        const double ez = -wk[IW_DZ * S + sl], bt = wk[IW_BT * S + sl];
-        if (!(isfinite(psi) && isfinite(dpsi) && isfinite(ez) && isfinite(bt))) bad = 1;
-        if (rec_snap) {
-          snap[OUT_PSI * N + id] = psi; snap[OUT_ERBT * N + id] = -dpsi;
-          snap[OUT_EZ * N + id] = ez; snap[OUT_BT * N + id] = bt;
-          snap[OUT_RHO * N + id] = r; snap[OUT_UR * N + id] = u;
+        const unsigned hs = (unsigned)SID[S + sl];
+        const int j = JX[S + sl];
+        const D2 f = W[wi + IW_F * S + sl];
+        const double u = W[wi + IW_UC * S + sl].x, bb = Wh[2 * (wi + IW_BB * S + sl)];
+        double dz = Wh[2 * (wi + IW_ZB * S + sl)];
+        D2 a2 = d2(0.0, 0.0);
+        if (has_laser) a2 = W[wi + IW_A2 * S + sl];
+        const D2 fp = Sc[(unsigned)(IS_N + IS_F) * S + hs];
+        const double r = sri[rx(p0 + k)];
+        double bp;
+        if (j >= 0) {
+          // the electrons' d_zeta psi and B^(p) between their rings
+          D2 zl = W[IW_ZB * S + pslot(max(j - 1, 0), C, div)], zh = W[IW_ZB * S + pslot(min(j, N - 1), C, div)];
+          if (j == 0) zl = d2(dza_e, 0.0);
+          if (j == N) zh = d2(0.0, bN / edge_e);
+          const double t = interval_t(sre, N, edge_e, r, j);
+          dz += (1.0 - t) * zl.x + t * zh.x;
+          bp = (1.0 - t) * zl.y + t * zh.y;
+        } else {
+          bp = bN / r;
         }
-        if (rec_last) {
-          last[OUT_PSI * N + id] = psi; last[OUT_ERBT * N + id] = -dpsi;
-          last[OUT_EZ * N + id] = ez; last[OUT_BT * N + id] = bt;
-          last[OUT_RHO * N + id] = r; last[OUT_UR * N + id] = u;
-        }
-        if (do_push) {
-          const double pb = wk[IW_PB * S + sl];
-          const double a2 = has_laser ? wk[IW_A2 * S + sl] : 0.0;
-          const double da2 = has_laser ? wk[IW_DA2 * S + sl] : 0.0;
-          const double gm = (1.0 + u * u + pb * pb + qq2 * a2) / (2.0 * pb);   // eq. motion_4
-          const double f_r = u / pb;
-          const double f_u = -(qm * (gm * dpsi / pb - bt) + q24 * da2 / pb);
-          double pr = f_r, pu = f_u;
-          if (n > 0) { pr = frp[id]; pu = fup[id]; }
-          double rn = r + dxi * (1.5 * f_r - 0.5 * pr);
-          double un = u + dxi * (1.5 * f_u - 0.5 * pu);
-          double sr_ = f_r, su = f_u;
-          if (rn < 0.0) { rn = -rn; un = -un; sr_ = -sr_; su = -su; }
-          if (!(isfinite(rn) && isfinite(un))) bad = 1;
-          rn_s[id] = rn;
-          un_s[id] = un;
-          fr_s[id] = sr_;
-          fu_s[id] = su;
-        }
+        finish(1, sl, hs, r, u, f, dz, bb + bp, a2, fp);
       }
     }
     if (tid == 0) {
       const dd pa = dd_add({s_sc[SC_PAH], s_sc[SC_PAL]}, {s_sc[SC_N + SC_PAH], s_sc[SC_N + SC_PAL]});
       const dd za = dd_add({s_sc[SC_DZH], s_sc[SC_DZL]}, {s_sc[SC_N + SC_DZH], s_sc[SC_N + SC_DZL]});
-      I.axis[2 * n] = dd_round(pa);
-      I.axis[2 * n + 1] = -dd_round(za);
+      gptr(I.axis)[2 * n] = dd_round(pa);
+      gptr(I.axis)[2 * n + 1] = -dd_round(za);
     }
     if (__syncthreads_or(bad)) {      // breakdown: stop at this slice, its state kept
       if (tid == 0) { I.ctl[CTL_BREAK] = n; I.ctl[CTL_NEXT] = n; I.ctl[CTL_CUR] = cur; }
@@ -856,7 +805,8 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
 // constants (when asked) and the rest state of both species in buffer 0
 __global__ void ions_init_kernel(WakeIons J, const double* __restrict__ r0, const double* __restrict__ dr,
                                  const double* __restrict__ dens, int constants) {
-  const int N = J.N;
+  const int N = J.N, C = J.C;
+  const size_t S = (size_t)C * NT;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j == 0) {
     J.ctl[CTL_CUR] = 0;
@@ -865,28 +815,24 @@ __global__ void ions_init_kernel(WakeIons J, const double* __restrict__ r0, cons
     J.ctl[CTL_FAULT] = 0;
   }
   if (j >= N) return;
-  double* const cst = const_cast<double*>(J.cst);
+  const unsigned hs = pslot(j, C, slot_div(C));
+  D2* const cst = reinterpret_cast<D2*>(const_cast<double*>(J.cst));
   if (constants) {
     const double r = r0[j], d = dr[j];
     const double nd = dens ? dens[j] : 1.0;
     const double w = nd * r * d;                  // eq. macroparticle_weight
     const dd lr = dd_log(r);
-    cst[IK_W * N + j] = w;
-    cst[IK_WH * N + j] = w / 2.0 - nd * d * d / 8.0;   // modified self weight
-    cst[IK_R0 * N + j] = r;
-    cst[IK_IR0 * N + j] = 1.0 / r;
-    cst[IK_LNH * N + j] = lr.hi;
-    cst[IK_LNL * N + j] = lr.lo;
-    cst[IK_DR * N + j] = d;
+    cst[IK_W * S + hs] = d2(w, w / 2.0 - nd * d * d / 8.0);   // and the modified self weight
+    cst[IK_R0 * S + hs] = d2(r, 1.0 / r);
+    cst[IK_LN * S + hs] = d2(lr.hi, lr.lo);
+    const_cast<double*>(J.cst)[2 * IK_DR * S + hs] = d;
   }
-  const double r = cst[IK_R0 * N + j];
+  const double r = cst[IK_R0 * S + hs].x;
   for (int s = 0; s < 2; ++s) {
-    double* const st = J.st[0] + (size_t)s * IS_N * N;
-    st[IS_RHO * N + j] = r;
-    st[IS_U * N + j] = 0.0;
-    st[IS_FR * N + j] = 0.0;
-    st[IS_FU * N + j] = 0.0;
-    J.ord[(size_t)s * N + j] = j;
+    D2* const st = reinterpret_cast<D2*>(J.st[0]) + (size_t)s * IS_N * S;
+    st[IS_RU * S + hs] = d2(r, 0.0);
+    st[IS_F * S + hs] = d2(0.0, 0.0);
+    J.ord[(size_t)s * S + hs] = j;
   }
 }
 
@@ -894,47 +840,54 @@ __global__ void ions_init_kernel(WakeIons J, const double* __restrict__ r0, cons
 // words reset), from its constants
 __global__ void ions_reset_kernel(const WakeIons* __restrict__ insts) {
   const WakeIons& J = insts[blockIdx.y];
-  const int N = J.N;
+  const int N = J.N, C = J.C;
+  const size_t S = (size_t)C * NT;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     J.ctl[CTL_CUR] = 0;
     J.ctl[CTL_BREAK] = -1;
     J.ctl[CTL_NEXT] = 0;
     J.ctl[CTL_FAULT] = 0;
   }
+  const unsigned div = slot_div(C);
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < N; j += gridDim.x * blockDim.x) {
-    const double r = J.cst[IK_R0 * N + j];
+    const unsigned hs = pslot(j, C, div);
+    const double r = reinterpret_cast<const D2*>(J.cst)[IK_R0 * S + hs].x;
     for (int s = 0; s < 2; ++s) {
-      double* const st = J.st[0] + (size_t)s * IS_N * N;
-      st[IS_RHO * N + j] = r;
-      st[IS_U * N + j] = 0.0;
-      st[IS_FR * N + j] = 0.0;
-      st[IS_FU * N + j] = 0.0;
-      J.ord[(size_t)s * N + j] = j;
+      D2* const st = reinterpret_cast<D2*>(J.st[0]) + (size_t)s * IS_N * S;
+      st[IS_RU * S + hs] = d2(r, 0.0);
+      st[IS_F * S + hs] = d2(0.0, 0.0);
+      J.ord[(size_t)s * S + hs] = j;
     }
   }
 }
 
 __global__ void ions_get_state_kernel(WakeIons J, int sp, double* __restrict__ out) {
-  const int N = J.N;
+  const int N = J.N, C = J.C;
+  const size_t S = (size_t)C * NT;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= N) return;
-  const double* st = J.st[J.ctl[CTL_CUR] & 1] + (size_t)sp * IS_N * N;
-  for (int q = 0; q < IS_N; ++q) out[(size_t)q * N + j] = st[(size_t)q * N + j];
+  const unsigned hs = pslot(j, C, slot_div(C));
+  const D2* st = reinterpret_cast<const D2*>(J.st[J.ctl[CTL_CUR] & 1]) + (size_t)sp * IS_N * S;
+  const D2 a = st[IS_RU * S + hs], f = st[IS_F * S + hs];
+  out[j] = a.x;
+  out[(size_t)N + j] = a.y;
+  out[(size_t)2 * N + j] = f.x;
+  out[(size_t)3 * N + j] = f.y;
 }
 
 __global__ void ions_set_state_kernel(WakeIons J, int sp, const double* __restrict__ rho,
                                       const double* __restrict__ u, const double* __restrict__ fr,
                                       const double* __restrict__ fu, int slice) {
-  const int N = J.N;
+  const int N = J.N, C = J.C;
+  const size_t S = (size_t)C * NT;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int b = J.ctl[CTL_CUR] & 1;
   if (j < N) {
-    double* st = J.st[b] + (size_t)sp * IS_N * N;
-    st[IS_RHO * N + j] = rho[j];
-    st[IS_U * N + j] = u[j];
-    st[IS_FR * N + j] = fr ? fr[j] : 0.0;
-    st[IS_FU * N + j] = fu ? fu[j] : 0.0;
-    J.ord[(size_t)sp * N + j] = j;      // order found again at the next slice
+    const unsigned hs = pslot(j, C, slot_div(C));
+    D2* st = reinterpret_cast<D2*>(J.st[b]) + (size_t)sp * IS_N * S;
+    st[IS_RU * S + hs] = d2(rho[j], u[j]);
+    st[IS_F * S + hs] = d2(fr ? fr[j] : 0.0, fu ? fu[j] : 0.0);
+    J.ord[(size_t)sp * S + hs] = j;      // order found again at the next slice
   }
   if (j == 0) {
     J.ctl[CTL_BREAK] = -1;
