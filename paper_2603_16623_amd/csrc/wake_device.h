@@ -364,39 +364,41 @@ __device__ __forceinline__ Pack<NF> row_suffix_incl(Pack<NF> inc, Op op) {
   if (M > 8) { const Pack<NF> o = dpp_pack<0x108>(inc); if (lr + 8 < M) inc = op(inc, o); }
   return inc;
 }
-// Inclusive prefix over the 64 lanes of the wave.
+// Inclusive prefix over the 64 lanes of the wave: within the rows, then each
+// odd row takes the row before it (DPP row_bcast:15), then the upper half the
+// lower (row_bcast:31).
 template <int NF, class Op>
 __device__ __forceinline__ Pack<NF> wave_prefix_incl(const Pack<NF>& x, Op op) {
   Pack<NF> inc = row_prefix_incl<16>(x, op);
   const int row = (threadIdx.x & 63) >> 4;
-  const Pack<NF> t0 = lane_pack(inc, 15), t1 = lane_pack(inc, 31), t2 = lane_pack(inc, 47);
-  const Pack<NF> t01 = op(t0, t1);
-  const Pack<NF> t012 = op(t01, t2);
-  const Pack<NF> pre = pick(row == 1, t0, pick(row == 2, t01, t012));
-  if (row > 0) inc = op(pre, inc);
+  const Pack<NF> o1 = dpp_pack<0x142>(inc);
+  if (row & 1) inc = op(o1, inc);
+  const Pack<NF> o2 = dpp_pack<0x143>(inc);
+  if (row >= 2) inc = op(o2, inc);
   return inc;
 }
-// Inclusive suffix over the 64 lanes of the wave.
+// Inclusive suffix over the 64 lanes of the wave (there is no DPP broadcast
+// towards lower rows: lane reads).
 template <int NF, class Op>
 __device__ __forceinline__ Pack<NF> wave_suffix_incl(const Pack<NF>& x, Op op) {
   Pack<NF> inc = row_suffix_incl<16>(x, op);
   const int row = (threadIdx.x & 63) >> 4;
-  const Pack<NF> t1 = lane_pack(inc, 16), t2 = lane_pack(inc, 32), t3 = lane_pack(inc, 48);
-  const Pack<NF> t23 = op(t2, t3);
-  const Pack<NF> t123 = op(t1, t23);
-  const Pack<NF> post = pick(row == 0, t123, pick(row == 1, t23, t3));
-  if (row < 3) inc = op(inc, post);
+  const Pack<NF> t1 = lane_pack(inc, 16), t3 = lane_pack(inc, 48);
+  const Pack<NF> o1 = pick(row < 2, t1, t3);
+  if (!(row & 1)) inc = op(inc, o1);
+  const Pack<NF> o2 = lane_pack(inc, 32);
+  if (row < 2) inc = op(inc, o2);
   return inc;
 }
-// Combined wave totals, read by every lane from `lds` (NW packs of NF,
+// Combined wave totals, read by every lane from `lds` (aw <= NW packs of NF,
 // starting at lds + off, stride S): exclusive prefix for this wave and the
 // total.  NW <= 16.
 template <int NW, int NF, class Op>
 __device__ __forceinline__ void waves_prefix(const double* lds, int off, int S, const Pack<NF>& ident, Op op,
-                                             Pack<NF>& pre, Pack<NF>& total) {
+                                             Pack<NF>& pre, Pack<NF>& total, int aw) {
   const int lane = threadIdx.x & 63;
   Pack<NF> a = ident;
-  if (lane < NW) {
+  if (lane < aw) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) a.v[i] = lds[lane * S + off + i];
   }
@@ -407,10 +409,10 @@ __device__ __forceinline__ void waves_prefix(const double* lds, int off, int S, 
 }
 template <int NW, int NF, class Op>
 __device__ __forceinline__ void waves_suffix(const double* lds, int off, int S, const Pack<NF>& ident, Op op,
-                                             Pack<NF>& suf, Pack<NF>& total) {
+                                             Pack<NF>& suf, Pack<NF>& total, int aw) {
   const int lane = threadIdx.x & 63;
   Pack<NF> a = ident;
-  if (lane < NW) {
+  if (lane < aw) {
 #pragma unroll
     for (int i = 0; i < NF; ++i) a.v[i] = lds[lane * S + off + i];
   }
@@ -420,6 +422,11 @@ __device__ __forceinline__ void waves_suffix(const double* lds, int off, int S, 
   total = lane_pack(a, 0);
 }
 
+// Workgroup scans.  The elements of waves aw, aw + 1, ... are the identity:
+// those waves leave the wave scan out and only take the totals (a scan is
+// bound by the SIMDs' issue, so with few rings the idle waves would slow the
+// others down).  aw is the same in every thread, 1 <= aw <= NT / 64.
+
 // Exclusive prefix over the workgroup in thread order.  op(earlier, later)
 // must be associative; ident must satisfy op(ident, x) == x exactly.
 // `lds` holds NT/64 packs.  Every thread also receives the total.  With
@@ -427,20 +434,23 @@ __device__ __forceinline__ void waves_suffix(const double* lds, int off, int S, 
 // `lds` again before another barrier has been passed by every thread.
 template <int NT, int NF, class Op, bool TAIL = true>
 __device__ __forceinline__ Pack<NF> block_prefix(const Pack<NF>& x, const Pack<NF>& ident, Op op,
-                                                 double* lds, Pack<NF>& total) {
+                                                 double* lds, Pack<NF>& total, int aw = NT / 64) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
-  const Pack<NF> inc = wave_prefix_incl(x, op);
-  const Pack<NF> sh = dpp_pack<0x138>(inc);       // outside any condition: every lane active
-  const Pack<NF> ex = pick(lane == 0, ident, sh);
-  if (lane == 63) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  Pack<NF> ex = ident;
+  if (wv < aw) {
+    const Pack<NF> inc = wave_prefix_incl(x, op);
+    const Pack<NF> sh = dpp_pack<0x138>(inc);       // outside any condition on lanes: every lane active
+    ex = pick(lane == 0, ident, sh);
+    if (lane == 63) {
 #pragma unroll
-    for (int i = 0; i < NF; ++i) lds[wv * NF + i] = inc.v[i];
+      for (int i = 0; i < NF; ++i) lds[wv * NF + i] = inc.v[i];
+    }
   }
   __syncthreads();
   Pack<NF> pre;
-  waves_prefix<NW, NF>(lds, 0, NF, ident, op, pre, total);
+  waves_prefix<NW, NF>(lds, 0, NF, ident, op, pre, total, aw);
   if (TAIL) __syncthreads();
   return op(pre, ex);
 }
@@ -449,20 +459,23 @@ __device__ __forceinline__ Pack<NF> block_prefix(const Pack<NF>& x, const Pack<N
 // elements of threads t+1 .. NT-1 in thread order, op(lower, higher).
 template <int NT, int NF, class Op>
 __device__ __forceinline__ Pack<NF> block_suffix(const Pack<NF>& x, const Pack<NF>& ident, Op op,
-                                                 double* lds, Pack<NF>& total) {
+                                                 double* lds, Pack<NF>& total, int aw = NT / 64) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
-  const Pack<NF> inc = wave_suffix_incl(x, op);
-  const Pack<NF> sh = dpp_pack<0x130>(inc);
-  const Pack<NF> ex = pick(lane == 63, ident, sh);
-  if (lane == 0) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  Pack<NF> ex = ident;
+  if (wv < aw) {
+    const Pack<NF> inc = wave_suffix_incl(x, op);
+    const Pack<NF> sh = dpp_pack<0x130>(inc);
+    ex = pick(lane == 63, ident, sh);
+    if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < NF; ++i) lds[wv * NF + i] = inc.v[i];
+      for (int i = 0; i < NF; ++i) lds[wv * NF + i] = inc.v[i];
+    }
   }
   __syncthreads();
   Pack<NF> suf;
-  waves_suffix<NW, NF>(lds, 0, NF, ident, op, suf, total);
+  waves_suffix<NW, NF>(lds, 0, NF, ident, op, suf, total, aw);
   __syncthreads();
   return op(ex, suf);
 }
@@ -474,30 +487,34 @@ template <int NT, int NP, int NS, class OpP, class OpS, bool TAIL = true>
 __device__ __forceinline__ void block_prefix_suffix(const Pack<NP>& xp, const Pack<NP>& idP, OpP opP,
                                                     const Pack<NS>& xs, const Pack<NS>& idS, OpS opS,
                                                     double* lds, Pack<NP>& exP, Pack<NP>& totP,
-                                                    Pack<NS>& exS, Pack<NS>& totS) {
+                                                    Pack<NS>& exS, Pack<NS>& totS, int aw = NT / 64) {
   constexpr int NW = NT / 64;
   constexpr int NF = NP + NS;
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
-  const Pack<NP> ip = wave_prefix_incl(xp, opP);
-  const Pack<NS> is = wave_suffix_incl(xs, opS);
-  const Pack<NP> shp = dpp_pack<0x138>(ip);
-  const Pack<NS> shs = dpp_pack<0x130>(is);
-  const Pack<NP> ep = pick(lane == 0, idP, shp);
-  const Pack<NS> es = pick(lane == 63, idS, shs);
-  if (lane == 63) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  Pack<NP> ep = idP;
+  Pack<NS> es = idS;
+  if (wv < aw) {
+    const Pack<NP> ip = wave_prefix_incl(xp, opP);
+    const Pack<NS> is = wave_suffix_incl(xs, opS);
+    const Pack<NP> shp = dpp_pack<0x138>(ip);
+    const Pack<NS> shs = dpp_pack<0x130>(is);
+    ep = pick(lane == 0, idP, shp);
+    es = pick(lane == 63, idS, shs);
+    if (lane == 63) {
 #pragma unroll
-    for (int i = 0; i < NP; ++i) lds[wv * NF + i] = ip.v[i];
-  }
-  if (lane == 0) {
+      for (int i = 0; i < NP; ++i) lds[wv * NF + i] = ip.v[i];
+    }
+    if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < NS; ++i) lds[wv * NF + NP + i] = is.v[i];
+      for (int i = 0; i < NS; ++i) lds[wv * NF + NP + i] = is.v[i];
+    }
   }
   __syncthreads();
   Pack<NP> pre;
   Pack<NS> suf;
-  waves_prefix<NW, NP>(lds, 0, NF, idP, opP, pre, totP);
-  waves_suffix<NW, NS>(lds, NP, NF, idS, opS, suf, totS);
+  waves_prefix<NW, NP>(lds, 0, NF, idP, opP, pre, totP, aw);
+  waves_suffix<NW, NS>(lds, NP, NF, idS, opS, suf, totS, aw);
   if (TAIL) __syncthreads();
   exP = opP(pre, ep);
   exS = opS(es, suf);
@@ -519,6 +536,21 @@ struct DD2Op {
   __device__ __forceinline__ Pack<4> operator()(const Pack<4>& a, const Pack<4>& b) const {
     dd x = dd_add({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
     dd y = dd_add({a.v[2], a.v[3]}, {b.v[2], b.v[3]});
+    return {{x.hi, x.lo, y.hi, y.lo}};
+  }
+};
+
+// one and two double-doubles, with one two_sum each
+struct DD1FastOp {
+  __device__ __forceinline__ Pack<2> operator()(const Pack<2>& a, const Pack<2>& b) const {
+    const dd x = dd_add_fast({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
+    return {{x.hi, x.lo}};
+  }
+};
+struct DD2FastOp {
+  __device__ __forceinline__ Pack<4> operator()(const Pack<4>& a, const Pack<4>& b) const {
+    const dd x = dd_add_fast({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
+    const dd y = dd_add_fast({a.v[2], a.v[3]}, {b.v[2], b.v[3]});
     return {{x.hi, x.lo, y.hi, y.lo}};
   }
 };

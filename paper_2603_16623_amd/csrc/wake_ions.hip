@@ -58,14 +58,17 @@ constexpr int NMAX = WAKE_IONS_NMAX;
 
 // dynamic LDS: sorted radii of both species, sort ids, scan area, slice
 // constants (analytic source factors, then 16 scalars per species), the
-// slice's beam-table radii (when at most WAKE_BCAP of them)
+// slice's beam table
 struct IonsLds {
   static constexpr size_t r_off = 0;
   static constexpr size_t id_off = r_off + (size_t)2 * NMAX * sizeof(double);
   static constexpr size_t scan_off = id_off + (size_t)NMAX * sizeof(uint16_t);
   static constexpr size_t misc_off = scan_off + (size_t)NW * 16 * sizeof(double);
   static constexpr size_t br_off = misc_off + 64 * sizeof(double);
-  static constexpr size_t bytes = br_off + (size_t)WAKE_BCAP * sizeof(double);
+  // the slice's beam table: radii and cumulative charges of up to BOTH
+  // entries, radii alone of up to 2 BOTH
+  static constexpr int BOTH = 832;
+  static constexpr size_t bytes = br_off + (size_t)2 * BOTH * sizeof(double);
 };
 static_assert(IonsLds::bytes <= 160 * 1024, "two-species LDS");
 
@@ -314,15 +317,6 @@ __device__ __forceinline__ int rings_below(const double* ro, int lo, int n, doub
   return a;
 }
 
-// sums of two double-doubles, with one two_sum each
-struct DD2FastOp {
-  __device__ __forceinline__ Pack<4> operator()(const Pack<4>& a, const Pack<4>& b) const {
-    const dd x = dd_add_fast({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
-    const dd y = dd_add_fast({a.v[2], a.v[3]}, {b.v[2], b.v[3]});
-    return {{x.hi, x.lo, y.hi, y.lo}};
-  }
-};
-
 // a + t (b - a) of two double-doubles
 __device__ __forceinline__ dd dd_lerp(dd a, dd b, double t) {
   return dd_add_fast(a, dd_mul_d(dd_add_fast(b, dd_neg(a)), t));
@@ -342,6 +336,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
   const unsigned S = (unsigned)C * NT, div = slot_div(C);
   const int p0 = tid * C;
   const int cnt = N - p0 < 0 ? 0 : (N - p0 < C ? N - p0 : C);
+  const int aw = __builtin_amdgcn_readfirstlane(((N + C - 1) / C + 63) >> 6);   // waves with rings
   if (I.ctl[CTL_BREAK] >= 0) return;
   int cur = I.ctl[CTL_CUR];
   const int end = I.first + I.count;
@@ -372,13 +367,17 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
         s_misc[3 * tid + 2] = 2.0 / (A.w0 * A.w0);
       }
     }
-    // this slice's beam-table radii into LDS (read after the order phase's
-    // barriers; the previous slice's reads ended at its last barrier)
+    // this slice's beam table into LDS (read after the order phase's
+    // barriers; the previous slice's reads ended at its last barrier): a
+    // ring's charge read from device memory behind its search kept the waves
+    // in the beam 15 us behind the others at 7900 rings
     const int bt0 = I.nb ? I.boff[n] : 0;
     const int bm = I.nb ? I.boff[n + 1] - bt0 : 0;
-    const bool b_lds = bm <= WAKE_BCAP;
+    const bool b_both = bm <= IonsLds::BOTH, b_lds = bm <= 2 * IonsLds::BOTH;
     if (b_lds)
       for (int i = tid; i < bm; i += NT) s_br[i] = gptr(I.br)[bt0 + i];
+    if (b_both)
+      for (int i = tid; i < bm; i += NT) s_br[IonsLds::BOTH + i] = gptr(I.bcum)[bt0 + i];
     const GA<D2> Sc = uview(reinterpret_cast<const D2*>(I.st[cur]));
     const GA<D2> Sn = uview(reinterpret_cast<const D2*>(I.st[cur ^ 1]));
 
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     block_prefix_suffix<NT, 4, 4, DD2FastOp, DD2FastOp, true>(
         Pack<4>{{sw[0].hi, sw[0].lo, sw[1].hi, sw[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(),
         Pack<4>{{swl[0].hi, swl[0].lo, swl[1].hi, swl[1].lo}}, Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(),
-        s_scan, exP, totP, exS, totS);
+        s_scan, exP, totP, exS, totS, aw);
     // node tables: psi and d_rho psi of each species at its own rings
     #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
@@ -571,7 +570,10 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
         double lam = 0.0;
         if (bm > 0) {
           blo = b_lds ? count_below(s_br, blo, bm, r, k > 0) : count_below(brg, blo, bm, r, k > 0);
-          if (blo > 0) lam = bcq[blo - 1];
+          if (blo > 0) {
+            if (b_both) lam = s_br[IonsLds::BOTH + blo - 1];
+            else lam = bcq[blo - 1];
+          }
         }
         double a2 = 0.0, da2 = 0.0;
         #pragma unroll 1
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     }
     Pack<4> dzs, dzt;
     dzs = block_suffix<NT, 4>(Pack<4>{{szc0.hi, szc0.lo, szc1.hi, szc1.lo}},
-                              Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(), s_scan, dzt);
+                              Pack<4>{{0.0, 0.0, 0.0, 0.0}}, DD2FastOp(), s_scan, dzt, aw);
     // own d_zeta psi at each ring: the rings outside with w, the ring itself
     // with w - w^
     #pragma unroll
@@ -668,7 +670,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     // growing mode at the chunk start, decaying mode at the chunk end
     Pack<4> gp, gt, hx, ht;
     block_prefix_suffix<NT, 4, 4, FwdMatOp, BwdMatOp, true>(
-        G, mat_ident(), FwdMatOp(), mat_adj(G), mat_ident(), BwdMatOp(), s_scan, gp, gt, hx, ht);
+        G, mat_ident(), FwdMatOp(), mat_adj(G), mat_ident(), BwdMatOp(), s_scan, gp, gt, hx, ht, aw);
     const double W_ = gt.v[0];                // det[g_N, (0, 1)]
     const double iW = 1.0 / W_;
     const double gsa = gp.v[0], gsb = gp.v[2], hea = hx.v[1], heb = hx.v[3];
@@ -678,7 +680,7 @@ __global__ __launch_bounds__(NT) void ions_march_kernel(const WakeIons* __restri
     Pack<1> ep, et, dsf, dt;
     block_prefix_suffix<NT, 1, 1, SumOp<1>, SumOp<1>, true>(Pack<1>{{le}}, Pack<1>{{0.0}}, SumOp<1>(),
                                                            Pack<1>{{ld}}, Pack<1>{{0.0}}, SumOp<1>(),
-                                                           s_scan, ep, et, dsf, dt);
+                                                           s_scan, ep, et, dsf, dt, aw);
     const double bN = et.v[0] * iW;           // b_N = E_N / W (a_N = 0)
 
     // ---- fields out, push: electrons (backward), then ions ----

@@ -1683,6 +1683,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   double* const s_x = s_kr;                                   // gathered packs (cooperative)
   int* const s_ok = reinterpret_cast<int*>(s_misc + 62);
   uint64_t* const s_dmask = reinterpret_cast<uint64_t*>(s_misc + 32);   // NW words: the push's disorder flags
+  uint64_t* const s_bmask = reinterpret_cast<uint64_t*>(s_misc + 40);   // NW words: its breakdown flags
   // the same two as byte offsets into the LDS, for the cooperative fix-ups
   const int xo = (int)MarchLds<NT>::head_bytes();
   const int oko = (int)(reinterpret_cast<unsigned char*>(s_ok) - smem);
@@ -1774,8 +1775,9 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   // The per-thread sums of (w, w ln rho), ln rho as the state carries it.
   // The sums in the order the march itself would have left them in (so that
   // a solve split over several launches is bitwise the one-launch solve):
-  // chunks whose order the fix-up changed sum forward, the others backward
-  // as the push does.
+  // the weights always forward (they are summed again only when the chunk's
+  // order changed); w ln rho forward in chunks whose order the fix-up
+  // changed, backward in the others as the push does.
   dd sw = {0.0, 0.0}, swl = {0.0, 0.0};
   if (moved) {
     chunk_sums<NT>(I, cur, cnt, goff, ps, ident, lds_keys, s_perm, s_ki, sw, swl);
@@ -1787,8 +1789,12 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       const PV SB = pview(I.st[cur], ps);
       const double w = KC.ldh(RC_W, (unsigned)st_hs(SB, s), 0);
       const D2 l = SB.ld(RS_LN, s);
-      sw = dd_add_d(sw, w);
       swl = dd_add_fast(swl, dd_mul_d(dd{l.x, l.y}, w));
+    }
+    #pragma unroll 1
+    for (int k = 0; k < cnt; ++k) {
+      const PV SB = pview(I.st[cur], ps);
+      sw = dd_add_d(sw, KC.ldh(RC_W, (unsigned)st_hs(SB, WAKE_SLOT((unsigned)(k * NT + tid))), 0));
     }
   }
   // sums of the thread's own rings in the push's order (what a fix-up that
@@ -1798,6 +1804,11 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   int end = I.first + I.count;
   if (n < end) stage_slice<NT>(I, n, s_misc, s_br, s_bc);
   double bad = 0.0, dis = 0.0;
+  // one workgroup: what the push of slice n-1 left, known after its barriers
+  bool any_bad = false, any_dis = false;
+  bool new_sw = true;          // the chunks' weights changed since the last scan of them
+  dd S0 = {0.0, 0.0};          // weight of the chunks before this thread's
+  const int aw = __builtin_amdgcn_readfirstlane(((Ng + C - 1) / C + 63) >> 6);   // waves with rings
   int fix_rounds = 0;          // consecutive fix-up rounds at this slice head
   int cl_rounds = 0;           // of which over all members (cooperative)
   int unpushed = cur;          // buffer with the unpushed state of slice n-1
@@ -1805,11 +1816,12 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   for (;;) {
     // ---- Gauss/log prefix sum_{k<i} (w_k, w_k ln rho_k); flags of slice n-1 ----
     Pack<6> t6;
+    dd PT0;                           // w ln rho of the chunks before this thread's
     double my_dis = 0.0, bnd = 0.0;   // cooperative: this member's disorder, member boundaries out of order
-    Pack<6> pre = block_prefix<NT, 6, SliceHeadOp, false>(
-        Pack<6>{{sw.hi, sw.lo, swl.hi, swl.lo, bad, dis}}, Pack<6>{{0, 0, 0, 0, 0, 0}},
-        SliceHeadOp(), s_scanA, t6);
-    if (CL) {
+    if constexpr (CL) {
+      Pack<6> pre = block_prefix<NT, 6, SliceHeadOp, false>(
+          Pack<6>{{sw.hi, sw.lo, swl.hi, swl.lo, bad, dis}}, Pack<6>{{0, 0, 0, 0, 0, 0}},
+          SliceHeadOp(), s_scanA, t6, aw);
       // members' totals, their first and last keys in the current order (run
       // boundaries between members) and the time budget
       Pack<11> mine;
@@ -1841,6 +1853,8 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       if (cl.G <= 64) cl_prefix<6, 11, SliceHeadOp, 1>(s_x, 0, member, cl.G, Pack<6>{{0, 0, 0, 0, 0, 0}}, SliceHeadOp(), pg, t6);
       else cl_prefix<6, 11>(s_x, 0, member, cl.G, Pack<6>{{0, 0, 0, 0, 0, 0}}, SliceHeadOp(), pg, t6);
       pre = SliceHeadOp()(pg, pre);
+      S0 = {pre.v[0], pre.v[1]};
+      PT0 = {pre.v[2], pre.v[3]};
       if constexpr (GRID) {
         rho_mprev = member > 0 ? s_x[(member - 1) * 11 + 8] : -1.0;
         rho_mlast = s_x[member * 11 + 8];
@@ -1858,13 +1872,15 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       const bool stop = __syncthreads_or(m_stop) != 0;
       t6.v[5] += bnd;
       if (stop && t6.v[4] == 0.0) end = n;
+      any_bad = t6.v[4] != 0.0;
+      any_dis = t6.v[5] != 0.0;
     }
-    if (t6.v[4] != 0.0) {     // slice n-1 broke down: stop there
+    if (any_bad) {            // slice n-1 broke down: stop there
       if (tid == 0 && member == 0) { I.ctl[CTL_BREAK] = n - 1; I.ctl[CTL_CUR] = unpushed; I.ctl[CTL_NEXT] = n - 1; }
       return;
     }
     if (n == end) break;
-    if (t6.v[5] != 0.0) {     // pushed radii out of order: new order, then redo the prefix
+    if (any_dis) {            // pushed radii out of order: new order (then the members' prefix again)
       bool restage = true;    // the general fix-ups use the beam-table area of LDS
       double still = 0.0;      // cooperative: this member still out of order after the round
       if (tid == 0 && member == 0) atomicAdd(I.cnt + CNT_FIXUPS, 1ull);
@@ -1933,10 +1949,35 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       }
       if (restage) stage_slice<NT>(I, n, s_misc, s_br, s_bc);
       dis = still;
-      continue;
+      new_sw = true;
+      if (CL) continue;
     }
     fix_rounds = 0;
     cl_rounds = 0;
+    sw_push = sw;
+    if constexpr (!CL) {
+      // the prefix after any fix-up (its order decides the chunks' sums); the
+      // weights' part only when a chunk holds other rings than at the last
+      // one, and the flags came with the push: 1000 rings 1.96 -> 1.0 us for
+      // this scan, which had carried all six
+      if (new_sw) {
+        Pack<4> t4;
+        const Pack<4> pre = block_prefix<NT, 4, DD2FastOp, false>(
+            Pack<4>{{sw.hi, sw.lo, swl.hi, swl.lo}}, Pack<4>{{0, 0, 0, 0}}, DD2FastOp(), s_scanA, t4, aw);
+        S0 = {pre.v[0], pre.v[1]};
+        PT0 = {pre.v[2], pre.v[3]};
+        t6.v[2] = t4.v[2];
+        t6.v[3] = t4.v[3];
+        new_sw = false;
+      } else {
+        Pack<2> t2;
+        const Pack<2> pre = block_prefix<NT, 2, DD1FastOp, false>(Pack<2>{{swl.hi, swl.lo}}, Pack<2>{{0, 0}},
+                                                                  DD1FastOp(), s_scanA, t2, aw);
+        PT0 = {pre.v[0], pre.v[1]};
+        t6.v[2] = t2.v[0];
+        t6.v[3] = t2.v[1];
+      }
+    }
     const double psi_axis = dd_round(dd_sub({t6.v[2], t6.v[3]}, tot0));
     const bool do_push = n < I.n_xi - 1;
     const bool rec_snap = I.stride > 0 && (n % I.stride) == 0;
@@ -1955,7 +1996,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     const WAKE_GLOBAL double* const gQ = gptr(I.bcum) + bt0;
 
     // ---- pass B: psi family, sources, local quantities, chunk sums ----
-    dd S = {pre.v[0], pre.v[1]}, PT = {pre.v[2], pre.v[3]};
+    dd S = S0, PT = PT0;
     Pack<4> G = mat_ident();
     double Vw = 0.0;
     double l0a = 0.0, l0b = 0.0, l1a = 0.0, l1b = 0.0;
@@ -2117,11 +2158,11 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     }
 
     // ---- growing mode g (prefix) and decaying mode h (suffix) ----
-    Pack<5> gp, gt, hx, ht;
-    block_prefix_suffix<NT, 5, 5, FwdMatSumOp, BwdMatSumOp, false>(
-        Pack<5>{{G.v[0], G.v[1], G.v[2], G.v[3], Vw}}, Pack<5>{{1.0, 0.0, 0.0, 1.0, 0.0}},
-        FwdMatSumOp(), Pack<5>{{G.v[3], -G.v[1], -G.v[2], G.v[0], Vw}},
-        Pack<5>{{1.0, 0.0, 0.0, 1.0, 0.0}}, BwdMatSumOp(), s_scanB, gp, gt, hx, ht);
+    Pack<4> gp, gt;
+    Pack<5> hx, ht;
+    block_prefix_suffix<NT, 4, 5, FwdMatOp, BwdMatSumOp, false>(
+        G, mat_ident(), FwdMatOp(), Pack<5>{{G.v[3], -G.v[1], -G.v[2], G.v[0], Vw}},
+        Pack<5>{{1.0, 0.0, 0.0, 1.0, 0.0}}, BwdMatSumOp(), s_scanB, gp, gt, hx, ht, aw);
     if (GRID && ngB > 0) {
       // psi, E_r - B_theta and the beam field at this member's nodes (the
       // scans' barriers order the sums written in pass B before these reads)
@@ -2167,25 +2208,27 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
                        gp.v[0] * l1a + gp.v[2] * l1b, gp.v[1] * l1a + gp.v[3] * l1b,
                        k0 * mua + k2 * mub, k1 * mua + k3 * mub, k0 * l1a + k2 * l1b, k1 * l1a + k3 * l1b}};
       Pack<8> ab;
-      block_prefix<NT, 8, SumOp<8>, false>(part, Pack<8>{{0, 0, 0, 0, 0, 0, 0, 0}}, SumOp<8>(), s_scanA, ab);
+      block_prefix<NT, 8, SumOp<8>, false>(part, Pack<8>{{0, 0, 0, 0, 0, 0, 0, 0}}, SumOp<8>(), s_scanA, ab, aw);
       Pack<13> mine;
 #pragma unroll
-      for (int i = 0; i < 5; ++i) mine.v[i] = gt.v[i];
+      for (int i = 0; i < 4; ++i) mine.v[i] = gt.v[i];
+      mine.v[4] = ht.v[4];
 #pragma unroll
       for (int i = 0; i < 8; ++i) mine.v[5 + i] = ab.v[i];
       if (!cl_gather<13, false>(cl, mine, s_x, s_ok)) {
         if (tid == 0 && member == 0) I.ctl[CTL_FAULT] = 1;
         return;
       }
-      Pack<5> pg, sg;
-      if (cl.G <= 64) cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 1>(s_x, member, cl.G, pg, gt, sg, ht, e_in, d_in);
-      else cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 4>(s_x, member, cl.G, pg, gt, sg, ht, e_in, d_in);
-      gp = FwdMatSumOp()(pg, gp);
+      Pack<5> pg, sg, g5;
+      if (cl.G <= 64) cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 1>(s_x, member, cl.G, pg, g5, sg, ht, e_in, d_in);
+      else cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 4>(s_x, member, cl.G, pg, g5, sg, ht, e_in, d_in);
+      gp = FwdMatOp()(Pack<4>{{pg.v[0], pg.v[1], pg.v[2], pg.v[3]}}, gp);
+      gt = Pack<4>{{g5.v[0], g5.v[1], g5.v[2], g5.v[3]}};
       hx = BwdMatSumOp()(hx, sg);
     }
     const double W = gt.v[0];                 // det[g_N, (0,1)]
     const double iW = 1.0 / W;
-    const double Vtot = gt.v[4];
+    const double Vtot = ht.v[4];
     const double Vafter = hx.v[4];
     const double gsa = gp.v[0], gsb = gp.v[2];    // g at the chunk start
     const double hea = hx.v[1], heb = hx.v[3];    // h at the chunk end
@@ -2198,7 +2241,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     Pack<1> ep, et, dsf, dt;
     block_prefix_suffix<NT, 1, 1, SumOp<1>, SumOp<1>, false>(
         Pack<1>{{le}}, Pack<1>{{0.0}}, SumOp<1>(), Pack<1>{{lds}}, Pack<1>{{0.0}}, SumOp<1>(),
-        s_scanA, ep, et, dsf, dt);
+        s_scanA, ep, et, dsf, dt, aw);
     if (CL) {
       ep.v[0] = e_in + ep.v[0];
       dsf.v[0] = dsf.v[0] + d_in;
@@ -2218,7 +2261,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     double D = dsf.v[0];
     double nxt_r = INFINITY, last_r = INFINITY;
     int32_t nxt_i = 0x7fffffff, last_i = 0x7fffffff;
-    dd sw2 = {0.0, 0.0}, swl2 = {0.0, 0.0};
+    dd swl2 = {0.0, 0.0};
     double dis_l = 0.0;
     // loads run ahead (the march goes backward): the state of ring k-2 and
     // the constants of ring k-1 are requested while ring k is computed
@@ -2365,7 +2408,6 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         Sn.st(RS_F, goff + sl, d2(sr, su));
         Sn.st(RS_LN, goff + sl, d2(lr.hi, lr.lo));
         Sn.sti(RS_W, goff + sl, hs);
-        sw2 = dd_add_d(sw2, w);
         swl2 = dd_add_fast(swl2, dd_mul_d(lr, w));
         if (lds_keys) { s_kr[sl] = rn; s_ki[sl] = (uint16_t)id; }
         if (CL) { gptr(I.gk_r)[goff + sl] = rn; gptr(I.gk_i)[goff + sl] = id; }
@@ -2406,10 +2448,18 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     s_fr[tid] = nxt_r;
     s_fi[tid] = nxt_i;
     if (CL && do_push && cnt > 0 && p0 + cnt == Ng) { s_misc[48] = last_r; s_misc[49] = (double)last_i; }
+    if (!CL || stage_next) __syncthreads();   // every wave is done with this slice's table and constants
     if (stage_next) {
-      __syncthreads();        // every wave is done with this slice's table and constants
       stage_analytic<NT>(I, n + 1, s_misc);
       beam_store<NT>(nbs, s_br, s_bc);
+    }
+    if constexpr (!CL) {
+      // the push's flags, a bit per thread: breakdown, and its chunk out of
+      // order inside or against the next chunk's first key
+      if (do_push && cnt > 0 && tid + 1 < NT && !key_lt(last_r, last_i, s_fr[tid + 1], s_fi[tid + 1]))
+        dis_l = 1.0;
+      const uint64_t md = __ballot(dis_l != 0.0), mb = __ballot(bad != 0.0);
+      if ((tid & 63) == 0) { s_dmask[tid >> 6] = md; s_bmask[tid >> 6] = mb; }
     }
     // out of time: this slice is the launch's last (one clock read, broadcast;
     // cooperative members decide together at the next slice head)
@@ -2417,6 +2467,13 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       s_misc[63] = !CL && budget > 0 && (int64_t)(__builtin_amdgcn_s_memrealtime() - t_start) >= budget ? 1.0 : 0.0;
     __syncthreads();
     if (s_misc[63] != 0.0) end = n + 1;
+    if constexpr (!CL) {
+      const int lane = tid & 63;
+      uint64_t md = 0, mb = 0;
+      if (lane < NW) { md = s_dmask[lane]; mb = s_bmask[lane]; }
+      any_dis = __ballot(md != 0) != 0;
+      any_bad = __ballot(mb != 0) != 0;
+    }
     if (GRID && ngB > 0) {
       // E_z and B_theta at this member's nodes (after the barrier above)
       WAKE_GLOBAL double* const gout = gptr(I.grid) + 5 * gofs;
@@ -2466,12 +2523,10 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         chi_nodes<NT, CL>(gout, ngB, gscr, thr, msuf, (CL ? cl.G : 1) * NT, GN, g_begin + tid, g_end, all0);
       }
     }
-    if (do_push && cnt > 0 && tid + 1 < NT && !key_lt(last_r, last_i, s_fr[tid + 1], s_fi[tid + 1]))
-      dis_l = 1.0;
-    dis = dis_l;
-    if (!CL && lds_keys) {    // the chunks' flags for the fix-up at the next slice head
-      const uint64_t m = __ballot(dis_l != 0.0);
-      if ((tid & 63) == 0) s_dmask[tid >> 6] = m;
+    if constexpr (CL) {
+      if (do_push && cnt > 0 && tid + 1 < NT && !key_lt(last_r, last_i, s_fr[tid + 1], s_fi[tid + 1]))
+        dis_l = 1.0;
+      dis = dis_l;
     }
     unpushed = cur;
     if (do_push) {
@@ -2479,9 +2534,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       cur = nb;
       ident = true;
       push_keys = CL;
-      sw = sw2;
       swl = swl2;
-      sw_push = sw2;
       swl_push = swl2;
     }
     ++n;
