@@ -98,26 +98,28 @@ __device__ __noinline__ int cl_await(const WAKE_GLOBAL double* sp, double want, 
 
 // All-gather of NF doubles per member; member m's pack lands at s_x[m * NF].
 // Every thread of every member calls it at the same point of the march.
-// Thread 0 writes the member's pack (write-through stores), waits for them
-// to complete and then writes the pack's stamp, the round number; thread m
+// After a barrier of the member lane i of its first wave writes word i of its
+// pack, word(i), in one write-through store for all; the wave waits for it to
+// complete and then writes the pack's stamp, the round number; thread m
 // waits for member m's stamp of this round; then the member's threads copy
 // all packs, word by word across the lanes.  There is no shared counter:
 // every member's arrival is its own word.  FENCED also
 // publishes the plain device-memory writes before it (release fence before
 // the stamp) and makes the others' visible after it (acquire fence).
 // Returns false when a member gave up.
-template <int NF, bool FENCED = true>
-__device__ __forceinline__ bool cl_gather(Cluster& cl, const Pack<NF>& mine, double* s_x, int* s_ok) {
+template <int NF, bool FENCED, class F>
+__device__ __forceinline__ bool cl_gather_words(Cluster& cl, F word, double* s_x, int* s_ok) {
   static_assert(NF <= 15, "exchange packs hold 15 doubles and the stamp");
   const int buf = cl.round & 1;
   const double stamp = (double)cl.round;
   WAKE_GLOBAL double* const xd = gptr(cl.xd);
   if (threadIdx.x == 0) *s_ok = 1;
   __syncthreads();                                   // this member's writes of the round are issued
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     WAKE_GLOBAL double* slot = xd + ((size_t)buf * cl.G + cl.g) * 16;
-#pragma unroll
-    for (int i = 0; i < NF; ++i) __hip_atomic_store(slot + i, mine.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int lane = threadIdx.x;
+    const double v = word(lane);
+    if (lane < NF) __hip_atomic_store(slot + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (FENCED) {
       // release only: the XCD's L2 written back (the member's plain stores
       // are there after the barrier); the acquire half comes after the wait
@@ -128,7 +130,8 @@ __device__ __forceinline__ bool cl_gather(Cluster& cl, const Pack<NF>& mine, dou
       __builtin_amdgcn_s_waitcnt(0);
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
     }
-    __hip_atomic_store(xd + cl_stamp_at(cl.G, buf, cl.g), stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0)
+      __hip_atomic_store(xd + cl_stamp_at(cl.G, buf, cl.g), stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   const int m = threadIdx.x;
   if (m < cl.G) {
@@ -150,6 +153,17 @@ __device__ __forceinline__ bool cl_gather(Cluster& cl, const Pack<NF>& mine, dou
   }
   ++cl.round;
   return ok != 0;
+}
+
+// The same for a pack every thread of the first wave holds.
+template <int NF, bool FENCED = true>
+__device__ __forceinline__ bool cl_gather(Cluster& cl, const Pack<NF>& mine, double* s_x, int* s_ok) {
+  return cl_gather_words<NF, FENCED>(cl, [&](int lane) {
+    double v = mine.v[0];
+#pragma unroll
+    for (int i = 1; i < NF; ++i) v = lane == i ? mine.v[i] : v;
+    return v;
+  }, s_x, s_ok);
 }
 
 // Exclusive prefix over members (op(earlier, later)) of the packs gathered at

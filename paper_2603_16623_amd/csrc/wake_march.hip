@@ -1203,12 +1203,6 @@ __device__ __noinline__ void fix_order_lds(const WakeInst& I, double* s_scan, do
 // ---------------------------------------------------------------------------
 // the slice marcher
 // ---------------------------------------------------------------------------
-struct FwdMatSumOp {  // (forward matrix product: earlier applied first, running sum)
-  __device__ __forceinline__ Pack<5> operator()(const Pack<5>& a, const Pack<5>& b) const {
-    Pack<4> m = mat_mul({{b.v[0], b.v[1], b.v[2], b.v[3]}}, {{a.v[0], a.v[1], a.v[2], a.v[3]}});
-    return {{m.v[0], m.v[1], m.v[2], m.v[3], a.v[4] + b.v[4]}};
-  }
-};
 struct BwdMatSumOp {  // (index-order product of inverse transfers, running sum)
   __device__ __forceinline__ Pack<5> operator()(const Pack<5>& lo, const Pack<5>& hi) const {
     Pack<4> m = mat_mul({{lo.v[0], lo.v[1], lo.v[2], lo.v[3]}}, {{hi.v[0], hi.v[1], hi.v[2], hi.v[3]}});
@@ -1217,7 +1211,7 @@ struct BwdMatSumOp {  // (index-order product of inverse transfers, running sum)
 };
 // Cooperative instances: the transfer products and the source det-sums of
 // all members from one exchange.  Member m publishes (G_m, V_m), its
-// transfer product and v-sum in FwdMatSumOp form, and four vectors summed
+// transfer product and v-sum, and four vectors summed
 // over its chunks: A = sum Gl^T mu, B = sum Gl^T l1, A' = sum K^T mu,
 // B' = sum K^T l1 (Gl: the member's transfers before the chunk; K = adj(G)
 // Hl with G the chunk's product and Hl the member's inverse transfers after
@@ -1229,99 +1223,129 @@ struct BwdMatSumOp {  // (index-order product of inverse transfers, running sum)
 // forms from the gathered packs (NFT doubles each) its exclusive prefix pg
 // and suffix sg of the transfers (inverse transfers from the adjugates of
 // the published products, det = 1), their totals, and the det-sums of the
-// members before it (e_in) and after it (d_in).  Lane l of each wave takes
-// members MPL l .. MPL l + MPL-1 (G <= 64 MPL).
-struct FwdMatSumOp;
-struct BwdMatSumOp;
-template <int NFT, class FOp, class BOp, int MPL>
-__device__ __forceinline__ void cl_transfer_scan(const double* s_x, int g, int G, Pack<5>& pg, Pack<5>& gt,
-                                                 Pack<5>& sg, Pack<5>& ht, double& e_in, double& d_in) {
+// members before it (e_in) and after it (d_in).  Lane l of a wave takes
+// members MPL l .. MPL l + MPL-1 (G <= 64 MPL).  One wave goes forward and
+// another backward, each on a SIMD of its own, and they leave their results
+// in LDS (every wave doing both took 1.7 us at 40 members, 3.8 at 196).
+//
+// Forward: out[0..3] = pg, out[4] = e_in, out[5..8] = the total.
+template <int NFT, int MPL>
+__device__ __forceinline__ void cl_transfer_fwd(const double* s_x, int g, int G, double* out) {
   const int lane = threadIdx.x & 63;
-  const Pack<5> I5 = {{1.0, 0.0, 0.0, 1.0, 0.0}};
-  const FOp fop;
-  const BOp bop;
+  const FwdMatOp fop;
   auto fwd_of = [&](int m) {
     const double* q = s_x + m * NFT;
-    return Pack<5>{{q[0], q[1], q[2], q[3], q[4]}};
+    return Pack<4>{{q[0], q[1], q[2], q[3]}};
   };
-  auto bwd_of = [&](int m) {
-    const double* q = s_x + m * NFT;
-    return Pack<5>{{q[3], -q[1], -q[2], q[0], q[4]}};
-  };
-  Pack<5> bf = I5, bb = I5;
+  Pack<4> bf = mat_ident();
+  double bv = 0.0;
 #pragma unroll
   for (int j = 0; j < MPL; ++j)
-    if (MPL * lane + j < G) bf = fop(bf, fwd_of(MPL * lane + j));
-#pragma unroll
-  for (int j = MPL - 1; j >= 0; --j)
-    if (MPL * lane + j < G) bb = bop(bwd_of(MPL * lane + j), bb);
-  const Pack<5> incF = wave_prefix_incl(bf, fop), incB = wave_suffix_incl(bb, bop);
-  Pack<5> exF, exB;                     // the members before this lane's, after them
-#pragma unroll
-  for (int i = 0; i < 5; ++i) { exF.v[i] = lane_prev(incF.v[i]); exB.v[i] = lane_next(incB.v[i]); }
-  if (lane == 0) exF = I5;
-  if (lane == 63) exB = I5;
-  gt = lane_pack(incF, 63);
-  ht = lane_pack(incB, 0);
-  double vm[MPL], dtm[MPL], etm[MPL];
-  Pack<5> pg_l = I5, sg_l = I5;
-  Pack<5> x = exB;
-#pragma unroll
-  for (int j = MPL - 1; j >= 0; --j) {  // descending: the suffix after each member
-    const int m = MPL * lane + j;
-    vm[j] = x.v[4];
-    dtm[j] = 0.0;
-    if (m < G) {
-      const double* q = s_x + m * NFT;
-      const double h0 = x.v[1], h1 = x.v[3];
-      dtm[j] = -(h0 * q[9] + h1 * q[10]) + x.v[4] * (h0 * q[11] + h1 * q[12]);
-      if (m == g) sg_l = x;
-      x = bop(bwd_of(m), x);
+    if (MPL * lane + j < G) {
+      bf = fop(bf, fwd_of(MPL * lane + j));
+      bv += s_x[(MPL * lane + j) * NFT + 4];
     }
-  }
-  x = exF;
+  const Pack<4> inc = wave_prefix_incl(bf, fop);
+  const Pack<1> incV = wave_suffix_incl(Pack<1>{{bv}}, SumOp<1>());
+  Pack<4> x;                            // the members before this lane's
 #pragma unroll
-  for (int j = 0; j < MPL; ++j) {       // ascending: the prefix before each member
+  for (int i = 0; i < 4; ++i) x.v[i] = lane_prev(inc.v[i]);
+  double V = lane_next(incV.v[0]);      // v after them
+  if (lane == 0) x = mat_ident();
+  if (lane == 63) V = 0.0;
+  double vm[MPL], etm[MPL];
+#pragma unroll
+  for (int j = MPL - 1; j >= 0; --j) {
+    const int m = MPL * lane + j;
+    vm[j] = V;
+    if (m < G) V += s_x[m * NFT + 4];
+  }
+  Pack<4> pg = mat_ident();
+#pragma unroll
+  for (int j = 0; j < MPL; ++j) {
     const int m = MPL * lane + j;
     etm[j] = 0.0;
     if (m < G) {
       const double* q = s_x + m * NFT;
       const double g0 = x.v[0], g1 = x.v[2];
       etm[j] = (g0 * q[5] + g1 * q[6]) - vm[j] * (g0 * q[7] + g1 * q[8]);
-      if (m == g) pg_l = x;
+      if (m == g) pg = x;
       x = fop(x, fwd_of(m));
     }
   }
   static_assert(MPL == 1 || MPL == 4, "one or four members per lane");
-  double esum = etm[0], dsum = dtm[0];
-  if constexpr (MPL == 4) {
-    esum = (etm[0] + etm[1]) + (etm[2] + etm[3]);
-    dsum = (dtm[0] + dtm[1]) + (dtm[2] + dtm[3]);
-  }
+  double esum = etm[0];
+  if constexpr (MPL == 4) esum = (etm[0] + etm[1]) + (etm[2] + etm[3]);
   const Pack<1> eI = wave_prefix_incl(Pack<1>{{esum}}, SumOp<1>());
-  const Pack<1> dI = wave_suffix_incl(Pack<1>{{dsum}}, SumOp<1>());
-  double e_own = lane_prev(eI.v[0]), d_own = lane_next(dI.v[0]);
+  double e_own = lane_prev(eI.v[0]);
   if (lane == 0) e_own = 0.0;
-  if (lane == 63) d_own = 0.0;
-  const int lg = g / MPL, jg = g % MPL;
+  const int jg = g % MPL;
 #pragma unroll
-  for (int j = 0; j < MPL; ++j) {
+  for (int j = 0; j < MPL; ++j)
     if (j < jg) e_own += etm[j];
-    if (j > jg) d_own += dtm[j];
+  if (lane == g / MPL) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = pg.v[i];
+    out[4] = e_own;
   }
-  e_in = lane_pack(Pack<1>{{e_own}}, lg).v[0];
-  d_in = lane_pack(Pack<1>{{d_own}}, lg).v[0];
-  pg = lane_pack(pg_l, lg);
-  sg = lane_pack(sg_l, lg);
+  if (lane == 63) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[5 + i] = inc.v[i];
+  }
 }
-
-struct SliceHeadOp {  // (w, w ln rho) as double-doubles, then two flag counts
-  __device__ __forceinline__ Pack<6> operator()(const Pack<6>& a, const Pack<6>& b) const {
-    const dd x = dd_add_fast({a.v[0], a.v[1]}, {b.v[0], b.v[1]});
-    const dd y = dd_add_fast({a.v[2], a.v[3]}, {b.v[2], b.v[3]});
-    return {{x.hi, x.lo, y.hi, y.lo, a.v[4] + b.v[4], a.v[5] + b.v[5]}};
+// Backward: out[0..4] = sg (with the v-sum), out[5] = d_in, out[6..10] = the
+// total.
+template <int NFT, class BOp, int MPL>
+__device__ __forceinline__ void cl_transfer_bwd(const double* s_x, int g, int G, double* out) {
+  const int lane = threadIdx.x & 63;
+  const Pack<5> I5 = {{1.0, 0.0, 0.0, 1.0, 0.0}};
+  const BOp bop;
+  auto bwd_of = [&](int m) {
+    const double* q = s_x + m * NFT;
+    return Pack<5>{{q[3], -q[1], -q[2], q[0], q[4]}};
+  };
+  Pack<5> bb = I5;
+#pragma unroll
+  for (int j = MPL - 1; j >= 0; --j)
+    if (MPL * lane + j < G) bb = bop(bwd_of(MPL * lane + j), bb);
+  const Pack<5> inc = wave_suffix_incl(bb, bop);
+  Pack<5> x;                            // the members after this lane's
+#pragma unroll
+  for (int i = 0; i < 5; ++i) x.v[i] = lane_next(inc.v[i]);
+  if (lane == 63) x = I5;
+  double dtm[MPL];
+  Pack<5> sg = I5;
+#pragma unroll
+  for (int j = MPL - 1; j >= 0; --j) {
+    const int m = MPL * lane + j;
+    dtm[j] = 0.0;
+    if (m < G) {
+      const double* q = s_x + m * NFT;
+      const double h0 = x.v[1], h1 = x.v[3];
+      dtm[j] = -(h0 * q[9] + h1 * q[10]) + x.v[4] * (h0 * q[11] + h1 * q[12]);
+      if (m == g) sg = x;
+      x = bop(bwd_of(m), x);
+    }
   }
-};
+  double dsum = dtm[0];
+  if constexpr (MPL == 4) dsum = (dtm[0] + dtm[1]) + (dtm[2] + dtm[3]);
+  const Pack<1> dI = wave_suffix_incl(Pack<1>{{dsum}}, SumOp<1>());
+  double d_own = lane_next(dI.v[0]);
+  if (lane == 63) d_own = 0.0;
+  const int jg = g % MPL;
+#pragma unroll
+  for (int j = 0; j < MPL; ++j)
+    if (j > jg) d_own += dtm[j];
+  if (lane == g / MPL) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) out[i] = sg.v[i];
+    out[5] = d_own;
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) out[6 + i] = inc.v[i];
+  }
+}
 
 template <int NT>
 struct MarchLds {
@@ -1803,9 +1827,11 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   int n = I.first;
   int end = I.first + I.count;
   if (n < end) stage_slice<NT>(I, n, s_misc, s_br, s_bc);
-  double bad = 0.0, dis = 0.0;
-  // one workgroup: what the push of slice n-1 left, known after its barriers
+  double bad = 0.0;
+  // what the push of slice n-1 left in this workgroup, known after its barriers
   bool any_bad = false, any_dis = false;
+  double still = 0.0, had = 0.0;   // cooperative: this member out of order after a round, had one before the meeting
+  dd Sm = {0.0, 0.0}, S0b = {0.0, 0.0};   // cooperative: its weight, and before this thread's chunk in it
   bool new_sw = true;          // the chunks' weights changed since the last scan of them
   dd S0 = {0.0, 0.0};          // weight of the chunks before this thread's
   const int aw = __builtin_amdgcn_readfirstlane(((Ng + C - 1) / C + 63) >> 6);   // waves with rings
@@ -1815,19 +1841,48 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
 
   for (;;) {
     // ---- Gauss/log prefix sum_{k<i} (w_k, w_k ln rho_k); flags of slice n-1 ----
-    Pack<6> t6;
+    dd psi_tot;                       // sum of w ln rho
     dd PT0;                           // w ln rho of the chunks before this thread's
     double my_dis = 0.0, bnd = 0.0;   // cooperative: this member's disorder, member boundaries out of order
     if constexpr (CL) {
-      Pack<6> pre = block_prefix<NT, 6, SliceHeadOp, false>(
-          Pack<6>{{sw.hi, sw.lo, swl.hi, swl.lo, bad, dis}}, Pack<6>{{0, 0, 0, 0, 0, 0}},
-          SliceHeadOp(), s_scanA, t6, aw);
-      // members' totals, their first and last keys in the current order (run
-      // boundaries between members) and the time budget
-      Pack<11> mine;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) mine.v[i] = t6.v[i];
-      if (tid == 0) {
+      // a member whose push came out of order inside its range sorts its
+      // blocks before it meets the others: they need not meet again for it
+      if (any_dis && n < end) {
+        if (tid == 0) atomicAdd(I.cnt + CNT_CL_LOCAL, 1ull);
+        const int st = 16 * P <= lo_cap ? cl_fix_local_lds<NT>(as_global(I), member, ident, lo)
+                                        : cl_fix_local<NT>(as_global(I), member, ident);
+        still = st ? 1.0 : 0.0;
+        had = 1.0;
+        ident = false;
+        push_keys = false;
+        bool changed = false;
+        for (int k = 0; k < cnt; ++k) changed |= WAKE_MOVED(gperm[goff + k * NT + tid], k);
+        if (changed) chunk_sums<NT>(I, cur, cnt, goff, ps, ident, lds_keys, s_perm, s_ki, sw, swl);
+        new_sw = true;
+      }
+      if (new_sw) {
+        Pack<4> t4;
+        const Pack<4> pre = block_prefix<NT, 4, DD2FastOp, false>(
+            Pack<4>{{sw.hi, sw.lo, swl.hi, swl.lo}}, Pack<4>{{0, 0, 0, 0}}, DD2FastOp(), s_scanA, t4, aw);
+        S0b = {pre.v[0], pre.v[1]};
+        PT0 = {pre.v[2], pre.v[3]};
+        Sm = {t4.v[0], t4.v[1]};
+        psi_tot = {t4.v[2], t4.v[3]};
+        new_sw = false;
+      } else {
+        Pack<2> t2;
+        const Pack<2> pre = block_prefix<NT, 2, DD1FastOp, false>(Pack<2>{{swl.hi, swl.lo}}, Pack<2>{{0, 0}},
+                                                                  DD1FastOp(), s_scanA, t2, aw);
+        PT0 = {pre.v[0], pre.v[1]};
+        psi_tot = {t2.v[0], t2.v[1]};
+      }
+      // members' totals, flags (breakdown, still out of order after its own
+      // round, whether it had one), their first and last keys in the current
+      // order (run boundaries between members) and the time budget
+      constexpr int HF = 12;
+      Pack<HF> mine = {{Sm.hi, Sm.lo, psi_tot.hi, psi_tot.lo, any_bad ? 1.0 : 0.0, still, 0.0, 0.0, 0.0, 0.0,
+                        0.0, had}};
+      if (tid < 64) {
         if (push_keys) {       // the push's keys of the first and the last position, kept in LDS
           mine.v[6] = s_fr[0];
           mine.v[7] = (double)s_fi[0];
@@ -1844,36 +1899,58 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         mine.v[10] = (budget > 0 && n > I.first &&
                       (int64_t)(__builtin_amdgcn_s_memrealtime() - t_start) >= budget) ? 1.0 : 0.0;
       }
-      if (!cl_gather<11, false>(cl, mine, s_x, s_ok)) {
+      if (!cl_gather<HF, false>(cl, mine, s_x, s_ok)) {
         if (tid == 0 && member == 0) I.ctl[CTL_FAULT] = 1;
         return;
       }
-      Pack<6> pg;
-      my_dis = t6.v[5];
-      if (cl.G <= 64) cl_prefix<6, 11, SliceHeadOp, 1>(s_x, 0, member, cl.G, Pack<6>{{0, 0, 0, 0, 0, 0}}, SliceHeadOp(), pg, t6);
-      else cl_prefix<6, 11>(s_x, 0, member, cl.G, Pack<6>{{0, 0, 0, 0, 0, 0}}, SliceHeadOp(), pg, t6);
-      pre = SliceHeadOp()(pg, pre);
-      S0 = {pre.v[0], pre.v[1]};
-      PT0 = {pre.v[2], pre.v[3]};
+      // one wave per question, the answers through LDS (every wave on all of
+      // them took 2.4 us at 40 members, 3.3 at 196)
+      const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+      double* const s_res = s_scanB;
+      if (wv < 2) {            // w ln rho, w: the members before this one, all of them
+        const Pack<2> z = {{0.0, 0.0}};
+        Pack<2> pg, tg;
+        const int off = wv == 0 ? 2 : 0;
+        if (cl.G <= 64) cl_prefix<2, HF, DD1FastOp, 1>(s_x, off, member, cl.G, z, DD1FastOp(), pg, tg);
+        else cl_prefix<2, HF, DD1FastOp, 4>(s_x, off, member, cl.G, z, DD1FastOp(), pg, tg);
+        if ((tid & 63) == 0) {
+          s_res[4 * wv] = pg.v[0]; s_res[4 * wv + 1] = pg.v[1];
+          s_res[4 * wv + 2] = tg.v[0]; s_res[4 * wv + 3] = tg.v[1];
+        }
+      } else if (wv == 2) {    // flags, a member out of time, member boundaries out of order
+        bool fb = false, fs = false, ft = false, fh = false, fo = false;
+        for (int m = tid & 63; m < cl.G; m += 64) {
+          const double* q = s_x + m * HF;
+          fb |= q[4] != 0.0;
+          fs |= q[5] != 0.0;
+          ft |= q[10] != 0.0;
+          fh |= q[11] != 0.0;
+          fo |= m + 1 < cl.G && key_lt(q[HF + 6], (int32_t)q[HF + 7], q[8], (int32_t)q[9]);
+        }
+        const int f = (__any(fb) ? 1 : 0) | (__any(fs) ? 2 : 0) | (__any(ft) ? 4 : 0) | (__any(fh) ? 8 : 0) |
+                      (__any(fo) ? 16 : 0);
+        if ((tid & 63) == 0) s_res[8] = (double)f;
+      }
+      __syncthreads();
+      PT0 = dd_add_fast({s_res[0], s_res[1]}, PT0);
+      psi_tot = {s_res[2], s_res[3]};
+      S0 = dd_add_fast({s_res[4], s_res[5]}, S0b);
+      const int flags = __builtin_amdgcn_readfirstlane((int)s_res[8]);
       if constexpr (GRID) {
-        rho_mprev = member > 0 ? s_x[(member - 1) * 11 + 8] : -1.0;
-        rho_mlast = s_x[member * 11 + 8];
+        rho_mprev = member > 0 ? s_x[(member - 1) * HF + 8] : -1.0;
+        rho_mlast = s_x[member * HF + 8];
       }
-      // a member out of time; boundaries between members out of order (thread
-      // m looks at member m and the one after it)
-      bool m_stop = false, m_bnd = false;
-      if (tid < cl.G) {
-        const int m = tid;
-        m_stop = s_x[m * 11 + 10] != 0.0;
-        m_bnd = m + 1 < cl.G && key_lt(s_x[(m + 1) * 11 + 6], (int32_t)s_x[(m + 1) * 11 + 7], s_x[m * 11 + 8],
-                                       (int32_t)s_x[m * 11 + 9]);
+      my_dis = still;
+      bnd = (flags & 16) ? 1.0 : 0.0;
+      any_bad = (flags & 1) != 0;
+      any_dis = (flags & 18) != 0;
+      if ((flags & 4) && !any_bad) end = n;
+      if (fix_rounds == 0 && (flags & 8)) {
+        // the members' own round before the meeting
+        fix_rounds = 1;
+        if (!any_dis && !any_bad && n != end && tid == 0 && member == 0) atomicAdd(I.cnt + CNT_FIXUPS, 1ull);
       }
-      bnd = __syncthreads_or(m_bnd) ? 1.0 : 0.0;
-      const bool stop = __syncthreads_or(m_stop) != 0;
-      t6.v[5] += bnd;
-      if (stop && t6.v[4] == 0.0) end = n;
-      any_bad = t6.v[4] != 0.0;
-      any_dis = t6.v[5] != 0.0;
+      __syncthreads();         // the answers are read before a scan writes there again
     }
     if (any_bad) {            // slice n-1 broke down: stop there
       if (tid == 0 && member == 0) { I.ctl[CTL_BREAK] = n - 1; I.ctl[CTL_CUR] = unpushed; I.ctl[CTL_NEXT] = n - 1; }
@@ -1882,18 +1959,19 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     if (n == end) break;
     if (any_dis) {            // pushed radii out of order: new order (then the members' prefix again)
       bool restage = true;    // the general fix-ups use the beam-table area of LDS
-      double still = 0.0;      // cooperative: this member still out of order after the round
+      still = 0.0;
       if (tid == 0 && member == 0) atomicAdd(I.cnt + CNT_FIXUPS, 1ull);
       if (CL) {
         // disorder inside members only: up to two member-local block rounds
-        // (members in order skip them); across member boundaries, or left
+        // (the first before the meeting; members in order skip them); across
+        // member boundaries, or left
         // over, block rounds over all members; after two of these that leave
         // disorder the sort by segments, then the bitonic network
         restage = false;
         if (bnd == 0.0 && fix_rounds < 2 && cl_rounds == 0) {
           if (my_dis == 0.0) {
             ++fix_rounds;
-            dis = 0.0;
+            any_bad = any_dis = false;
             continue;
           }
           if (tid == 0) atomicAdd(I.cnt + CNT_CL_LOCAL, 1ull);
@@ -1948,12 +2026,15 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         swl = swl_push;
       }
       if (restage) stage_slice<NT>(I, n, s_misc, s_br, s_bc);
-      dis = still;
       new_sw = true;
-      if (CL) continue;
+      if (CL) {
+        any_bad = any_dis = false;
+        continue;
+      }
     }
     fix_rounds = 0;
     cl_rounds = 0;
+    still = had = 0.0;
     sw_push = sw;
     if constexpr (!CL) {
       // the prefix after any fix-up (its order decides the chunks' sums); the
@@ -1966,19 +2047,17 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
             Pack<4>{{sw.hi, sw.lo, swl.hi, swl.lo}}, Pack<4>{{0, 0, 0, 0}}, DD2FastOp(), s_scanA, t4, aw);
         S0 = {pre.v[0], pre.v[1]};
         PT0 = {pre.v[2], pre.v[3]};
-        t6.v[2] = t4.v[2];
-        t6.v[3] = t4.v[3];
+        psi_tot = {t4.v[2], t4.v[3]};
         new_sw = false;
       } else {
         Pack<2> t2;
         const Pack<2> pre = block_prefix<NT, 2, DD1FastOp, false>(Pack<2>{{swl.hi, swl.lo}}, Pack<2>{{0, 0}},
                                                                   DD1FastOp(), s_scanA, t2, aw);
         PT0 = {pre.v[0], pre.v[1]};
-        t6.v[2] = t2.v[0];
-        t6.v[3] = t2.v[1];
+        psi_tot = {t2.v[0], t2.v[1]};
       }
     }
-    const double psi_axis = dd_round(dd_sub({t6.v[2], t6.v[3]}, tot0));
+    const double psi_axis = dd_round(dd_sub(psi_tot, tot0));
     const bool do_push = n < I.n_xi - 1;
     const bool rec_snap = I.stride > 0 && (n % I.stride) == 0;
     const bool rec_last = n == end - 1;
@@ -2207,24 +2286,43 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       Pack<8> part = {{gp.v[0] * mua + gp.v[2] * mub, gp.v[1] * mua + gp.v[3] * mub,
                        gp.v[0] * l1a + gp.v[2] * l1b, gp.v[1] * l1a + gp.v[3] * l1b,
                        k0 * mua + k2 * mub, k1 * mua + k3 * mub, k0 * l1a + k2 * l1b, k1 * l1a + k3 * l1b}};
-      Pack<8> ab;
-      block_prefix<NT, 8, SumOp<8>, false>(part, Pack<8>{{0, 0, 0, 0, 0, 0, 0, 0}}, SumOp<8>(), s_scanA, ab, aw);
-      Pack<13> mine;
+      const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+      if (wv < aw) {                     // sums over the wave, then (by the publishing lanes) the waves
+        const Pack<8> ws = wave_prefix_incl(part, SumOp<8>());
+        if ((tid & 63) == 63) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) mine.v[i] = gt.v[i];
-      mine.v[4] = ht.v[4];
+          for (int i = 0; i < 8; ++i) s_scanA[wv * 8 + i] = ws.v[i];
+        }
+      }
+      auto word = [&](int l) {
+        double v = ht.v[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) mine.v[5 + i] = ab.v[i];
-      if (!cl_gather<13, false>(cl, mine, s_x, s_ok)) {
+        for (int i = 0; i < 4; ++i) v = l == i ? gt.v[i] : v;
+        if (l >= 5 && l < 13) {
+          v = 0.0;
+          for (int w = 0; w < aw; ++w) v += s_scanA[w * 8 + l - 5];
+        }
+        return v;
+      };
+      if (!cl_gather_words<13, false>(cl, word, s_x, s_ok)) {
         if (tid == 0 && member == 0) I.ctl[CTL_FAULT] = 1;
         return;
       }
-      Pack<5> pg, sg, g5;
-      if (cl.G <= 64) cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 1>(s_x, member, cl.G, pg, g5, sg, ht, e_in, d_in);
-      else cl_transfer_scan<13, FwdMatSumOp, BwdMatSumOp, 4>(s_x, member, cl.G, pg, g5, sg, ht, e_in, d_in);
-      gp = FwdMatOp()(Pack<4>{{pg.v[0], pg.v[1], pg.v[2], pg.v[3]}}, gp);
-      gt = Pack<4>{{g5.v[0], g5.v[1], g5.v[2], g5.v[3]}};
-      hx = BwdMatSumOp()(hx, sg);
+      double* const s_res = s_scanB;
+      if (wv == 0) {
+        if (cl.G <= 64) cl_transfer_fwd<13, 1>(s_x, member, cl.G, s_res);
+        else cl_transfer_fwd<13, 4>(s_x, member, cl.G, s_res);
+      } else if (wv == 1) {
+        if (cl.G <= 64) cl_transfer_bwd<13, BwdMatSumOp, 1>(s_x, member, cl.G, s_res + 16);
+        else cl_transfer_bwd<13, BwdMatSumOp, 4>(s_x, member, cl.G, s_res + 16);
+      }
+      __syncthreads();
+      gp = FwdMatOp()(Pack<4>{{s_res[0], s_res[1], s_res[2], s_res[3]}}, gp);
+      e_in = s_res[4];
+      gt = Pack<4>{{s_res[5], s_res[6], s_res[7], s_res[8]}};
+      hx = BwdMatSumOp()(hx, Pack<5>{{s_res[16], s_res[17], s_res[18], s_res[19], s_res[20]}});
+      d_in = s_res[21];
+      ht = Pack<5>{{s_res[22], s_res[23], s_res[24], s_res[25], s_res[26]}};
     }
     const double W = gt.v[0];                 // det[g_N, (0,1)]
     const double iW = 1.0 / W;
@@ -2448,12 +2546,12 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     s_fr[tid] = nxt_r;
     s_fi[tid] = nxt_i;
     if (CL && do_push && cnt > 0 && p0 + cnt == Ng) { s_misc[48] = last_r; s_misc[49] = (double)last_i; }
-    if (!CL || stage_next) __syncthreads();   // every wave is done with this slice's table and constants
+    __syncthreads();          // every wave is done with this slice's table and constants
     if (stage_next) {
       stage_analytic<NT>(I, n + 1, s_misc);
       beam_store<NT>(nbs, s_br, s_bc);
     }
-    if constexpr (!CL) {
+    {
       // the push's flags, a bit per thread: breakdown, and its chunk out of
       // order inside or against the next chunk's first key
       if (do_push && cnt > 0 && tid + 1 < NT && !key_lt(last_r, last_i, s_fr[tid + 1], s_fi[tid + 1]))
@@ -2467,7 +2565,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       s_misc[63] = !CL && budget > 0 && (int64_t)(__builtin_amdgcn_s_memrealtime() - t_start) >= budget ? 1.0 : 0.0;
     __syncthreads();
     if (s_misc[63] != 0.0) end = n + 1;
-    if constexpr (!CL) {
+    {
       const int lane = tid & 63;
       uint64_t md = 0, mb = 0;
       if (lane < NW) { md = s_dmask[lane]; mb = s_bmask[lane]; }
@@ -2522,11 +2620,6 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
         }
         chi_nodes<NT, CL>(gout, ngB, gscr, thr, msuf, (CL ? cl.G : 1) * NT, GN, g_begin + tid, g_end, all0);
       }
-    }
-    if constexpr (CL) {
-      if (do_push && cnt > 0 && tid + 1 < NT && !key_lt(last_r, last_i, s_fr[tid + 1], s_fi[tid + 1]))
-        dis_l = 1.0;
-      dis = dis_l;
     }
     unpushed = cur;
     if (do_push) {
