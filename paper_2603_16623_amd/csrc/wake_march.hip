@@ -202,12 +202,13 @@ __device__ __forceinline__ int ion_find(const float* nodes, int N, double r, int
   // the common case, at most four nodes up from the guess (the interval of
   // the ring before, in radial order), from one round of independent reads:
   // the gallop's smallest answer took four dependent ones of ~65 cycles, in
-  // every lane's slowest order
-  const float n0 = nodes[j], n1 = nodes[min(j + 1, N)], n2 = nodes[min(j + 2, N)], n3 = nodes[min(j + 3, N)],
-              n4 = nodes[min(j + 4, N)];
+  // every lane's slowest order.  Past the last node (nodes[N]) come four
+  // that compare false.
+  const float n0 = nodes[j], n1 = nodes[j + 1], n2 = nodes[j + 2], n3 = nodes[j + 3], n4 = nodes[j + 4];
   if (n0 <= x) {
-    a = min(j + (n1 <= x ? 1 : 0) + (n2 <= x ? 1 : 0) + (n3 <= x ? 1 : 0) + (n4 <= x ? 1 : 0), N);
-    if (a < j + 4 || a == N) return a;
+    const int c = (n1 <= x ? 1 : 0) + (n2 <= x ? 1 : 0) + (n3 <= x ? 1 : 0) + (n4 <= x ? 1 : 0);
+    a = j + c;
+    if (c < 4) return a;
     int step = 4;                            // nodes[a] <= x
     for (;;) {
       b = a + step;
@@ -232,6 +233,19 @@ __device__ __forceinline__ int ion_find(const float* nodes, int N, double r, int
     if (nodes[m] <= x) a = m; else b = m;
   }
   return a;
+}
+// The same with a window [w0, w0 + wn) of the nodes in LDS.  From a guess j
+// inside it the search ends at the window's edge at most; from one outside it
+// looks only for radii inside.  The exact search in ion_fields starts from
+// the record of the interval returned.
+__device__ __forceinline__ int ion_find_window(const float* nodes, int w0, int wn, double r, int j) {
+  int jr = j - w0;
+  if (jr < 0 || jr >= wn) {
+    const float x = (float)r;
+    if (!(nodes[0] <= x && x < nodes[wn - 1])) return j;
+    jr = jr < 0 ? 0 : wn - 1;
+  }
+  return w0 + ion_find(nodes, wn - 1, r, jr);
 }
 // ---------------------------------------------------------------------------
 // ring-set initialisation: weights, ln r0, ion interval records, state
@@ -1369,7 +1383,8 @@ struct MarchLds {
            (size_t)WAKE_SORTCAP * sizeof(uint16_t);
   }
   // ion interval nodes as floats (instances with keys in LDS: N <= KCAP)
-  static constexpr size_t ion_bytes() { return ((size_t)(KCAP + 1) * sizeof(float) + 15) & ~(size_t)15; }
+  // and four past them
+  static constexpr size_t ion_bytes() { return ((size_t)(KCAP + 5) * sizeof(float) + 15) & ~(size_t)15; }
   static constexpr size_t bytes() { return head_bytes() + key_bytes() + region_bytes() + ion_bytes(); }
 };
 // one workgroup's LDS must fit the 160 KiB of a compute unit
@@ -1654,9 +1669,10 @@ __device__ __forceinline__ double analytic_lam(const double* s_misc, int n_an, d
   return lam;
 }
 
-template <int NT, bool CL, int GM>
+template <int NT, bool CL, int GM, bool WIN>
 __device__ __forceinline__ void march(const WakeInst& I, int member, const int32_t* queue, unsigned char* smem) {
   // GM: 0 no field grid, 1 field grid, 2 field grid with the chi deposit
+  // WIN: cooperative, with a window of the ion nodes in LDS
   constexpr bool GRID = GM > 0;
   constexpr bool CHI = GM > 1;
   constexpr int NW = NT / 64;
@@ -1708,6 +1724,7 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   int* const s_ok = reinterpret_cast<int*>(s_misc + 62);
   uint64_t* const s_dmask = reinterpret_cast<uint64_t*>(s_misc + 32);   // NW words: the push's disorder flags
   uint64_t* const s_bmask = reinterpret_cast<uint64_t*>(s_misc + 40);   // NW words: its breakdown flags
+  int32_t* const s_win = reinterpret_cast<int32_t*>(s_misc + 24);       // cooperative: the member's first and last ion interval
   // the same two as byte offsets into the LDS, for the cooperative fix-ups
   const int xo = (int)MarchLds<NT>::head_bytes();
   const int oko = (int)(reinterpret_cast<unsigned char*>(s_ok) - smem);
@@ -1783,7 +1800,20 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   const bool has_laser = I.has_laser != 0;
   // ion interval nodes in LDS (float) for the interval search of pass B;
   // read there after the slice-head scan's barriers
-  const bool lds_ion = N <= KCAP;      // the interval nodes fit the LDS table
+  // Cooperative members of more than two rings per thread (WIN) keep a window
+  // of them around the member's rings, moved when its rings leave it: the
+  // search in device memory, a dependent chain per ring, from each ring's own
+  // interval at the previous slice, made the slowest member late.  Eight
+  // rings per thread: 20000 rings on 5 members 57.1 -> 54.5 us per slice
+  // once the rings moved (39.0 -> 39.6 while they rest), 200000 on 49
+  // 55.0 -> 52.8, 40 served requests 191 -> 182 ms.  With one or two rings
+  // per thread that interval comes with the ring, whose record's load need
+  // not wait for a search (20000 rings on 40 members 19.2 us per slice, 20.0
+  // with the window); a variant of its own, since the window's scalars alone
+  // spill registers there.
+  const bool lds_ion = CL ? WIN : N <= KCAP;        // the interval nodes in LDS
+  const int wn = WIN ? min(N + 1, KCAP + 1) : N + 1;
+  int w0 = WIN ? min(max(goff + P / 2 - wn / 2, 0), N + 1 - wn) : 0;
   int hint0 = goff + p0 + 1;           // interval of the thread's first ring (at rest: its node's)
   // field-grid node records in the LDS beyond the layout (read after the
   // slice-head scan's barriers)
@@ -1794,7 +1824,8 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     for (int i = tid; i < 3 * I.grid_n; i += NT) s_gt[i] = t[i];
   }
   if (lds_ion)
-    for (int j = tid; j <= N; j += NT) s_ion[j] = (float)IV.R[j * WAKE_ION_REC + IR_LO];
+    for (int j = tid; j < wn + 4; j += NT)
+      s_ion[j] = j < wn ? (float)IV.R[(w0 + j) * WAKE_ION_REC + IR_LO] : __builtin_nanf("");
 
   // The per-thread sums of (w, w ln rho), ln rho as the state carries it.
   // The sums in the order the march itself would have left them in (so that
@@ -2106,7 +2137,8 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     int jn = 0;
     if (cnt > 0) {
       x_wc = KC.ld(RC_W, (unsigned)x_hs);
-      jn = lds_ion ? ion_find(s_ion, N, x_ru.x, hint0) : x_hn;
+      jn = !lds_ion ? x_hn : WIN ? ion_find_window(s_ion, w0, wn, x_ru.x, hint0)
+                                : ion_find(s_ion, N, x_ru.x, hint0);
       ion_load(IV, jn, x_q);
     }
     // field grid: the interval owning each node hands the node its sums
@@ -2154,7 +2186,8 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       // the next ring's weights and ion record, into the registers just read
       if (k + 1 < cnt) {
         x_wc = KC.ld(RC_W, (unsigned)x_hs);
-        jn = lds_ion ? ion_find(s_ion, N, x_ru.x, h) : x_hn;
+        jn = !lds_ion ? x_hn : WIN ? ion_find_window(s_ion, w0, wn, x_ru.x, h)
+                                  : ion_find(s_ion, N, x_ru.x, h);
         ion_load(IV, jn, x_q);
       }
       if (GRID && rho >= gb_next) {
@@ -2220,6 +2253,10 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
       // ring: the next slice's search starts there)
       if (!lds_ion) Sn.sti(RS_W, Sn.ps + goff + sl, h);
       if (k == 0) hint0 = h;
+      if (WIN && wn <= N) {     // the member's first and last interval
+        if (p0 + k == 0) s_win[0] = h;
+        if (p0 + k == Ng - 1) s_win[1] = h;
+      }
     }
     if (GRID && ngB > 0 && cnt > 0 && p0 + cnt == Ng && (!CL || member == cl.G - 1)) {
       // nodes beyond the last ring: every ring below them
@@ -2547,6 +2584,16 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
     s_fi[tid] = nxt_i;
     if (CL && do_push && cnt > 0 && p0 + cnt == Ng) { s_misc[48] = last_r; s_misc[49] = (double)last_i; }
     __syncthreads();          // every wave is done with this slice's table and constants
+    if (WIN && wn <= N) {
+      // the window follows the member's rings: around them when one end left
+      // it (rings spread over more intervals than it holds: around their middle)
+      const int j0 = __builtin_amdgcn_readfirstlane(s_win[0]), j1 = __builtin_amdgcn_readfirstlane(s_win[1]);
+      const int want = min(max((j0 + j1) / 2 - wn / 2, 0), N + 1 - wn);
+      if ((j0 < w0 || j1 >= w0 + wn) && abs(want - w0) > wn / 8) {
+        w0 = want;
+        for (int j = tid; j < wn; j += NT) s_ion[j] = (float)IV.R[(w0 + j) * WAKE_ION_REC + IR_LO];
+      }
+    }
     if (stage_next) {
       stage_analytic<NT>(I, n + 1, s_misc);
       beam_store<NT>(nbs, s_br, s_bc);
@@ -2645,9 +2692,9 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
 
 // the cooperative march as a function of its own (its registers stay out of
 // the single-workgroup march, which is inlined into the kernel)
-template <int NT, int GM>
+template <int NT, int GM, bool WIN>
 __device__ __noinline__ void march_member(const WAKE_GLOBAL WakeInst* I, int member, const int32_t* queue) {
-  march<NT, true, GM>(*(const WakeInst*)I, member, queue, wake_lds);
+  march<NT, true, GM, WIN>(*(const WakeInst*)I, member, queue, wake_lds);
 }
 
 #ifndef WAKE_WAVES_PER_EU
@@ -2673,8 +2720,12 @@ void wake_march_kernel(const WakeInst* __restrict__ insts, int n_insts, int n_ta
     }
     const WakeInst& I = insts[lo];
     if (I.nt == NT) {
-      if (I.G > 1) march_member<NT, GM>(as_global(I), idx - I.task0, counter);
-      else march<NT, false, GM>(I, 0, counter, smem);
+      if (I.G > 1) {
+        if (I.C > 2) march_member<NT, GM, true>(as_global(I), idx - I.task0, counter);
+        else march_member<NT, GM, false>(as_global(I), idx - I.task0, counter);
+      } else {
+        march<NT, false, GM, false>(I, 0, counter, smem);
+      }
     }
     __syncthreads();
   }
