@@ -260,92 +260,6 @@ __device__ __forceinline__ int32_t cl_id(int32_t hs, int C, int P, double iP) {
 __device__ __forceinline__ bool k64_lt(double ra, uint64_t ka, double rb, uint64_t kb) {
   return (ra < rb) | ((ra == rb) & (ka < kb));
 }
-__device__ __forceinline__ uint64_t lane_xor64(uint64_t x, int lm) {
-  return ((uint64_t)lane_xor((uint32_t)(x >> 32), lm) << 32) | lane_xor((uint32_t)x, lm);
-}
-__device__ __forceinline__ uint64_t lane_next64(uint64_t x) {
-  return ((uint64_t)lane_next((uint32_t)(x >> 32)) << 32) | lane_next((uint32_t)x);
-}
-__device__ __forceinline__ uint64_t lane_prev64(uint64_t x) {
-  return ((uint64_t)lane_prev((uint32_t)(x >> 32)) << 32) | lane_prev((uint32_t)x);
-}
-
-// One wave sorts 256 keys held four per lane (lane l: keys 4l..4l+3) by
-// (radius, 64-bit word with the id in the high half): odd-even
-// transposition for up to 32 phases, then a bitonic network.  Returns false
-// when they were in order already (nothing moved).
-__device__ __forceinline__ bool sort_regs256(double* r, uint64_t* k) {
-  const int lane = threadIdx.x & 63;
-  bool ok = !k64_lt(r[1], k[1], r[0], k[0]) && !k64_lt(r[2], k[2], r[1], k[1]) &&
-            !k64_lt(r[3], k[3], r[2], k[2]);
-  {
-    const double nr = lane_next(r[0]);
-    const uint64_t nk = lane_next64(k[0]);
-    if (lane < 63) ok = ok && !k64_lt(nr, nk, r[3], k[3]);
-  }
-  if (__all(ok)) return false;
-  bool done = false;
-  #pragma unroll 1
-  for (int it = 0; it < 8 && !done; ++it) {
-#pragma unroll
-    for (int ph = 0; ph < 2; ++ph) {
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        if (k64_lt(r[j + 1], k[j + 1], r[j], k[j])) {
-          const double tr = r[j]; r[j] = r[j + 1]; r[j + 1] = tr;
-          const uint64_t tk = k[j]; k[j] = k[j + 1]; k[j + 1] = tk;
-        }
-      }
-      if (k64_lt(r[2], k[2], r[1], k[1])) {
-        const double tr = r[1]; r[1] = r[2]; r[2] = tr;
-        const uint64_t tk = k[1]; k[1] = k[2]; k[2] = tk;
-      }
-      const double nr = lane_next(r[0]), pr = lane_prev(r[3]);
-      const uint64_t nq = lane_next64(k[0]), pq = lane_prev64(k[3]);
-      const bool take_next = lane < 63 && k64_lt(nr, nq, r[3], k[3]);
-      const bool take_prev = lane > 0 && k64_lt(r[0], k[0], pr, pq);
-      if (take_next) { r[3] = nr; k[3] = nq; }
-      if (take_prev) { r[0] = pr; k[0] = pq; }
-    }
-    bool in_order = !k64_lt(r[1], k[1], r[0], k[0]) && !k64_lt(r[2], k[2], r[1], k[1]) &&
-                    !k64_lt(r[3], k[3], r[2], k[2]);
-    const double xr = lane_next(r[0]);
-    const uint64_t xq = lane_next64(k[0]);
-    if (lane < 63) in_order = in_order && !k64_lt(xr, xq, r[3], k[3]);
-    done = __all(in_order);
-  }
-  if (!done) {
-#pragma unroll
-    for (int kk = 2; kk <= 256; kk <<= 1) {
-#pragma unroll
-      for (int d = kk >> 1; d > 0; d >>= 1) {
-        if (d >= 4) {
-          const int lm = d >> 2;
-          const bool lower = (lane & lm) == 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const double pr = lane_xor(r[j], lm);
-            const uint64_t pq = lane_xor64(k[j], lm);
-            const bool up = ((4 * lane + j) & kk) == 0;
-            if (k64_lt(pr, pq, r[j], k[j]) == (lower == up)) { r[j] = pr; k[j] = pq; }
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (j & d) continue;
-            const int jj = j | d;
-            const bool up = ((4 * lane + j) & kk) == 0;
-            if (k64_lt(r[jj], k[jj], r[j], k[j]) == up) {
-              const double tr = r[j]; r[j] = r[jj]; r[jj] = tr;
-              const uint64_t tk = k[j]; k[j] = k[jj]; k[jj] = tk;
-            }
-          }
-        }
-      }
-    }
-  }
-  return true;
-}
 
 // One wave puts the positions [b0, b0 + 256) of a cooperative instance in
 // order: keys by slot in device memory (gk_r, gk_i), order perm by position
@@ -359,45 +273,56 @@ __device__ __noinline__ void cl_sort_block(int b0, int N, int C, int P, double i
                                            const WAKE_GLOBAL int32_t* src_at = nullptr) {
   const int lane = threadIdx.x & 63;
   double r[4];
-  uint64_t k[4];
+  uint32_t k[4];
   int sl[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
     sl[j] = -1;
     r[j] = INFINITY;
-    k[j] = ~0ull;
+    k[j] = ~0u;
     if (p < N) {
       sl[j] = cl_slot<NT>(p, C, P, iC, iP);
-      const int src = src_at ? src_at[p] : perm[sl[j]];
-      r[j] = gk_r[src];
-      k[j] = ((uint64_t)(uint32_t)gk_i[src] << 32) | (uint32_t)src;
+      k[j] = (uint32_t)(src_at ? src_at[p] : perm[sl[j]]);
+      r[j] = gk_r[k[j]];
     }
   }
-  if (!sort_regs256(r, k)) return;
+  if (!wave_sort256<false>(r, k, [&](uint32_t src) { return gk_i[src]; })) return;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
-    if (sl[j] >= 0 && p >= w_lo && p < w_hi) perm[sl[j]] = (int32_t)(uint32_t)(k[j] & 0xffffffffull);
+    // (a padding word here only when a radius is not finite: the slice broke down)
+    if (sl[j] >= 0 && p >= w_lo && p < w_hi) perm[sl[j]] = k[j] == ~0u ? sl[j] : (int32_t)k[j];
   }
 }
 
-// The same for keys held by position in LDS (L_r, L_k, positions [0, n)).
-__device__ __noinline__ void lds_sort_block(int b0, int n, double* L_r, uint64_t* L_k) {
+// The same for keys held by position in LDS (positions [0, n), radii at byte
+// offset lo, ids and slots at lk: as pointers they would be read by flat
+// loads), moved there; the wave's network carries each key's place in the
+// block.
+// MERGE: the two halves of the block are each in order.
+template <bool MERGE>
+__device__ __noinline__ void lds_sort_block(int b0, int n, int lo, int lk) {
+  double* const L_r = reinterpret_cast<double*>(wake_lds + lo);
+  uint64_t* const L_k = reinterpret_cast<uint64_t*>(wake_lds + lk);
   const int lane = threadIdx.x & 63;
   double r[4];
-  uint64_t k[4];
+  uint32_t k[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int p = b0 + 4 * lane + j;
-    r[j] = p < n ? L_r[p] : INFINITY;
-    k[j] = p < n ? L_k[p] : ~0ull;
+    const int q = wave_place<MERGE>(j);
+    r[j] = b0 + q < n ? L_r[b0 + q] : INFINITY;
+    k[j] = b0 + q < n ? (uint32_t)q : ~0u;
   }
-  if (!sort_regs256(r, k)) return;
+  auto id = [&](uint32_t q) { return (uint32_t)(L_k[b0 + q] >> 32); };
+  if (!wave_sort256<MERGE>(r, k, id)) return;
+  uint64_t v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = b0 + 4 * lane + j < n ? L_k[min(b0 + (int)(k[j] & 255u), n - 1)] : 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
-    if (p < n) { L_r[p] = r[j]; L_k[p] = k[j]; }
+    if (p < n) { L_r[p] = r[j]; L_k[p] = v[j]; }
   }
 }
 
@@ -664,10 +589,10 @@ __device__ __forceinline__ int cl_lds_blocks(const WakeInst& I, int g, bool firs
   }
   __syncthreads();
   #pragma unroll 1
-  for (int b = wave; b * 256 < Ng; b += NW) lds_sort_block(b * 256, Ng, L_r, L_k);
+  for (int b = wave; b * 256 < Ng; b += NW) lds_sort_block<false>(b * 256, Ng, lo, lo + 8 * P);
   __syncthreads();
   #pragma unroll 1
-  for (int b = wave; 128 + b * 256 < lim; b += NW) lds_sort_block(128 + b * 256, Ng, L_r, L_k);
+  for (int b = wave; 128 + b * 256 < lim; b += NW) lds_sort_block<true>(128 + b * 256, Ng, lo, lo + 8 * P);
   __syncthreads();
   int bad = 0;
   #pragma unroll 1

@@ -290,6 +290,200 @@ __device__ __forceinline__ double lane_xor(double x, int lm) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// lane_next and lane_prev of a radius with +inf after the last lane, -inf
+// before the first: no lane-edge cases in the compares
+__device__ __forceinline__ double lane_next_inf(double x) {
+  const uint64_t v = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = lane_next((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0x7ff00000u, (uint32_t)(v >> 32), 0x130, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double lane_prev_inf(double x) {
+  const uint64_t v = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = lane_prev((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0xfff00000u, (uint32_t)(v >> 32), 0x138, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// ---------------------------------------------------------------------------
+// 256 rings put in (radius, id) order by one wave: four per lane (lane l:
+// positions 4l..4l+3), r the radii, k a word that goes with each; positions
+// past the last ring hold +inf and k = ~0
+// ---------------------------------------------------------------------------
+// The order fix-ups are bound by vector issue (7900 rings on one workgroup:
+// 12 of 31 blocks out of order per slice, half of them by more than 32
+// positions), so the networks compare radii alone, one instruction where
+// (radius, id) took three and two scalar ones on the path to each exchange;
+// rings of equal radius, which hardly occur, are put in the order of their
+// ids afterwards.  Sorting network 2300 -> 1500 instructions, merge 650 ->
+// 400; 7900 rings once they cross 87.2 -> 80.3 us per slice, 20000 rings on 5
+// members 57 -> 52, on 40 members 32.0 -> 29.0, 4000 rings of two species
+// 82.5 -> 78.7.
+// Exchanges go by lane masks in scalar registers: left to itself the compiler
+// made branches of them, or masks of vector registers.
+__device__ __forceinline__ uint64_t lanes_lt(double a, double b) { return __builtin_amdgcn_ballot_w64(a < b); }
+__device__ __forceinline__ void wave_take(uint64_t m, double& r, uint32_t& k, double pr, uint32_t pk) {
+  const bool t = __builtin_amdgcn_inverse_ballot_w64(m);
+  r = t ? pr : r;
+  k = t ? pk : k;
+}
+__device__ __forceinline__ void wave_swap(uint64_t m, double& ra, uint32_t& ka, double& rb, uint32_t& kb) {
+  const double r = ra;
+  const uint32_t k = ka;
+  wave_take(m, ra, ka, rb, kb);
+  wave_take(m, rb, kb, r, k);
+}
+// lanes whose bits of x are all clear
+__device__ constexpr uint64_t lanes_clear(int x) {
+  uint64_t m = 0;
+  for (int l = 0; l < 64; ++l) m |= (uint64_t)((l & x) == 0) << l;
+  return m;
+}
+__device__ __forceinline__ bool wave_ascending(const double* r) {
+  const double x = lane_next_inf(r[0]);
+  return (lanes_lt(r[1], r[0]) | lanes_lt(r[2], r[1]) | lanes_lt(r[3], r[2]) | lanes_lt(x, r[3])) == 0;
+}
+// rings of equal radius (r ascending) in the order of id(k); whether any moved
+template <class IdOf>
+__device__ __forceinline__ bool wave_ties(const double* r, uint32_t* k, IdOf id) {
+  const double x = lane_next_inf(r[0]), w = lane_prev_inf(r[3]);
+  const bool e0 = (r[0] == r[1]) & (r[1] < INFINITY), e1 = (r[1] == r[2]) & (r[2] < INFINITY),
+             e2 = (r[2] == r[3]) & (r[3] < INFINITY), e3 = (r[3] == x) & (x < INFINITY);
+  if (!__any(e0 | e1 | e2 | e3)) return false;
+  const bool em = (r[0] == w) & (r[0] < INFINITY);
+  uint32_t i[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) i[j] = k[j] == ~0u ? ~0u : (uint32_t)id(k[j]);
+  bool moved = false;
+  // odd-even transposition within the runs of equal radii (at most 256 long)
+  #pragma unroll 1
+  for (int it = 0; it < 128; ++it) {
+    bool m = false;
+    auto swap = [&](int a, int b) {
+      uint32_t t = i[a]; i[a] = i[b]; i[b] = t;
+      t = k[a]; k[a] = k[b]; k[b] = t;
+      m = true;
+    };
+    if (e0 && i[1] < i[0]) swap(0, 1);
+    if (e2 && i[3] < i[2]) swap(2, 3);
+    if (e1 && i[2] < i[1]) swap(1, 2);
+    const uint32_t ni = lane_next(i[0]), nk = lane_next(k[0]), pi = lane_prev(i[3]), pk = lane_prev(k[3]);
+    if (e3 && ni < i[3]) { i[3] = ni; k[3] = nk; m = true; }
+    if (em && i[0] < pi) { i[0] = pi; k[0] = pk; m = true; }
+    if (!__any(m)) break;
+    moved = true;
+  }
+  return moved;
+}
+__device__ __forceinline__ void lanes_swap(int lm, uint32_t& a, uint32_t& b) {
+  const auto v = lm == 16 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                          : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = v[0];
+  b = v[1];
+}
+__device__ __forceinline__ void lanes_swap(int lm, double& ra, uint32_t& ka, double& rb, uint32_t& kb) {
+  const uint64_t x = (uint64_t)__double_as_longlong(ra), y = (uint64_t)__double_as_longlong(rb);
+  uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32), yl = (uint32_t)y, yh = (uint32_t)(y >> 32);
+  lanes_swap(lm, xl, yl);
+  lanes_swap(lm, xh, yh);
+  lanes_swap(lm, ka, kb);
+  ra = __longlong_as_double((long long)(((uint64_t)xh << 32) | xl));
+  rb = __longlong_as_double((long long)(((uint64_t)yh << 32) | yl));
+}
+// compare-exchange stage of a bitonic network at distance d, ascending where
+// (position & kk) == 0 (kk = 256: everywhere)
+__device__ __forceinline__ void wave_stage(double* r, uint32_t* k, int kk, int d) {
+  if (d >= 64) {
+    // partner 16 or 32 lanes away: two registers' pairs brought into lanes of
+    // their own (the swap exchanges the first's upper rows with the second's
+    // lower ones), exchanged there, and taken back
+    const uint64_t up = lanes_clear(kk >> 2 & 63);
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+      lanes_swap(d >> 2, r[j], k[j], r[j + 1], k[j + 1]);
+      wave_swap(~(lanes_lt(r[j + 1], r[j]) ^ up), r[j], k[j], r[j + 1], k[j + 1]);
+      lanes_swap(d >> 2, r[j], k[j], r[j + 1], k[j + 1]);
+    }
+  } else if (d >= 4) {                // partner in lane ^ (d / 4), same register
+    const int lm = d >> 2;
+    // the smaller stays where the lane is the lower one of an ascending pair
+    // or the upper one of a descending pair (kk >= 8 here: the same for a
+    // lane's four positions); equal radii stay
+    const uint64_t sm = ~(lanes_clear(lm) ^ lanes_clear(kk >> 2 & 63));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const double pr = lane_xor(r[j], lm);
+      const uint32_t pk = lane_xor(k[j], lm);
+      wave_take((lanes_lt(pr, r[j]) & sm) | (lanes_lt(r[j], pr) & ~sm), r[j], k[j], pr, pk);
+    }
+  } else {                            // partner in this lane
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j & d) continue;
+      const int jj = j | d;
+      const uint64_t up = kk < 4 ? ((j & kk) == 0 ? ~0ull : 0ull) : lanes_clear(kk >> 2 & 63);
+      wave_swap(~(lanes_lt(r[jj], r[j]) ^ up), r[j], k[j], r[jj], k[jj]);
+    }
+  }
+}
+// Place in the block of a lane's register j when it is loaded: its own
+// position; for a merge the second half in reverse, which makes the block
+// bitonic.
+template <bool MERGE>
+__device__ __forceinline__ int wave_place(int j) {
+  const int q = 4 * (threadIdx.x & 63) + j;
+  return MERGE && q >= 128 ? 383 - q : q;
+}
+// The block (loaded by wave_place) in order; false if it was already, and
+// then nothing may be written back.  Odd-even transposition first: the rings
+// of a run of length L reach their places within L phases and never cross a
+// run boundary, so blocks with short runs (the common case) are done after a
+// few phases.  Order checked every four phases; a block still out of order
+// after 32 phases goes through the full bitonic network.  MERGE: the two
+// halves are each in order, and the half-cleaning stages of a bitonic merge
+// do.
+template <bool MERGE, class IdOf>
+__device__ __forceinline__ bool wave_sort256(double* r, uint32_t* k, IdOf id) {
+  bool moved = true;
+  if constexpr (MERGE) {
+    // the last radius of the first half against the first of the second
+    const uint64_t v = (uint64_t)__double_as_longlong(r[3]);
+    const uint64_t x = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), 31) << 32 |
+                       (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, 31);
+    const uint64_t y = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), 63) << 32 |
+                       (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, 63);
+    if (lanes_lt(__longlong_as_double((long long)x), __longlong_as_double((long long)y)) != 0) return false;
+#pragma unroll
+    for (int d = 128; d > 0; d >>= 1) wave_stage(r, k, 256, d);
+  } else {
+    moved = !wave_ascending(r);
+    bool done = !moved;
+    #pragma unroll 1
+    for (int it = 0; it < 8 && !done; ++it) {
+#pragma unroll
+      for (int ph = 0; ph < 2; ++ph) {
+        // even phase: (0,1) (2,3); odd phase: (1,2) and (3 | next lane's 0)
+        wave_swap(lanes_lt(r[1], r[0]), r[0], k[0], r[1], k[1]);
+        wave_swap(lanes_lt(r[3], r[2]), r[2], k[2], r[3], k[3]);
+        wave_swap(lanes_lt(r[2], r[1]), r[1], k[1], r[2], k[2]);
+        const double nr = lane_next_inf(r[0]), pr = lane_prev_inf(r[3]);
+        const uint32_t nk = lane_next(k[0]), pk = lane_prev(k[3]);
+        wave_take(lanes_lt(nr, r[3]), r[3], k[3], nr, nk);      // the smaller of the pair
+        wave_take(lanes_lt(r[0], pr), r[0], k[0], pr, pk);      // the larger
+      }
+      done = wave_ascending(r);
+    }
+    if (!done) {
+#pragma unroll
+      for (int kk = 2; kk <= 256; kk <<= 1) {
+#pragma unroll
+        for (int d = kk >> 1; d > 0; d >>= 1) wave_stage(r, k, kk, d);
+      }
+    }
+  }
+  return wave_ties(r, k, id) || moved;
+}
+
 // ---------------------------------------------------------------------------
 // packs of doubles moved through cross-lane shuffles and LDS
 // ---------------------------------------------------------------------------

@@ -770,194 +770,32 @@ __device__ __forceinline__ bool pk_lt(double ra, uint32_t ka, double rb, uint32_
 }
 
 // One wave puts the positions [b0, b0 + 256) (clipped at N) in (rho, id)
-// order: four keys per lane, read through the current order perm, sorted by
-// a bitonic network over registers and lane exchanges, written back as the
-// new order of these positions.  A block already in order is left alone.
-template <int NT>
+// order: four keys per lane, read through the current order perm, written
+// back as the new order of these positions.  MERGE: the two halves of the
+// block are each in order.  A block already in order is left alone.
+template <int NT, bool MERGE>
 __device__ __forceinline__ void sort_block_wave(int b0, int N, int C, double iC, const double* kr,
                                                 const uint16_t* ki, uint16_t* perm) {
   const int lane = threadIdx.x & 63;
   double r[4];
   uint32_t k[4];
-  int sl[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int p = b0 + wave_place<MERGE>(j);
+    r[j] = INFINITY;
+    k[j] = ~0u;
+    if (p < N) {
+      k[j] = perm[pos_index<NT>(p, C, iC)];
+      r[j] = kr[k[j]];
+    }
+  }
+  auto id = [&](uint32_t src) { return ki[src]; };
+  if (!wave_sort256<MERGE>(r, k, id)) return;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int p = b0 + 4 * lane + j;
-    sl[j] = -1;
-    r[j] = INFINITY;
-    k[j] = 0xffffffffu;
-    if (p < N) {
-      sl[j] = pos_index<NT>(p, C, iC);
-      const unsigned src = perm[sl[j]];
-      r[j] = kr[src];
-      k[j] = ((uint32_t)ki[src] << 16) | src;
-    }
+    if (p < N) perm[pos_index<NT>(p, C, iC)] = (uint16_t)k[j];
   }
-  bool ok = !pk_lt(r[1], k[1], r[0], k[0]) && !pk_lt(r[2], k[2], r[1], k[1]) &&
-            !pk_lt(r[3], k[3], r[2], k[2]);
-  const double nr = __shfl_down(r[0], 1, 64);
-  const uint32_t nk = __shfl_down(k[0], 1, 64);
-  if (lane < 63) ok = ok && !pk_lt(nr, nk, r[3], k[3]);
-  if (__all(ok)) return;
-  // Odd-even transposition first: the rings of a run of length L reach
-  // their places within L phases and never cross a run boundary, so blocks
-  // with short runs (the common case) are done after a few phases.  Order
-  // checked every four phases; a block still out of order after 32 phases
-  // goes through the full bitonic network.
-  #pragma unroll 1
-  for (int it = 0; it < 8; ++it) {
-#pragma unroll
-    for (int ph = 0; ph < 2; ++ph) {
-      // even phase: (0,1) (2,3); odd phase: (1,2) and (3 | next lane's 0)
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        if (pk_lt(r[j + 1], k[j + 1], r[j], k[j])) {
-          const double tr = r[j]; r[j] = r[j + 1]; r[j + 1] = tr;
-          const uint32_t tk = k[j]; k[j] = k[j + 1]; k[j + 1] = tk;
-        }
-      }
-      if (pk_lt(r[2], k[2], r[1], k[1])) {
-        const double tr = r[1]; r[1] = r[2]; r[2] = tr;
-        const uint32_t tk = k[1]; k[1] = k[2]; k[2] = tk;
-      }
-      const double nr = lane_next(r[0]), pr = lane_prev(r[3]);
-      const uint32_t nq = lane_next(k[0]), pq = lane_prev(k[3]);
-      const bool take_next = lane < 63 && pk_lt(nr, nq, r[3], k[3]);    // keep the smaller
-      const bool take_prev = lane > 0 && pk_lt(r[0], k[0], pr, pq);     // keep the larger
-      if (take_next) { r[3] = nr; k[3] = nq; }
-      if (take_prev) { r[0] = pr; k[0] = pq; }
-    }
-    bool in_order = !pk_lt(r[1], k[1], r[0], k[0]) && !pk_lt(r[2], k[2], r[1], k[1]) &&
-                    !pk_lt(r[3], k[3], r[2], k[2]);
-    const double xr = lane_next(r[0]);
-    const uint32_t xq = lane_next(k[0]);
-    if (lane < 63) in_order = in_order && !pk_lt(xr, xq, r[3], k[3]);
-    if (__all(in_order)) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (sl[j] >= 0) perm[sl[j]] = (uint16_t)(k[j] & 0xffffu);
-      return;
-    }
-  }
-#pragma unroll
-  for (int kk = 2; kk <= 256; kk <<= 1) {
-#pragma unroll
-    for (int d = kk >> 1; d > 0; d >>= 1) {
-      if (d >= 4) {                 // partner in lane ^ (d / 4), same register
-        const int lm = d >> 2;
-        const bool lower = (lane & lm) == 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double pr = lane_xor(r[j], lm);
-          const uint32_t pq = lane_xor(k[j], lm);
-          const bool up = ((4 * lane + j) & kk) == 0;
-          if (pk_lt(pr, pq, r[j], k[j]) == (lower == up)) { r[j] = pr; k[j] = pq; }
-        }
-      } else {                      // partner in this lane
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (j & d) continue;
-          const int jj = j | d;
-          const bool up = ((4 * lane + j) & kk) == 0;
-          if (pk_lt(r[jj], k[jj], r[j], k[j]) == up) {
-            const double tr = r[j]; r[j] = r[jj]; r[jj] = tr;
-            const uint32_t tk = k[j]; k[j] = k[jj]; k[jj] = tk;
-          }
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (sl[j] >= 0) perm[sl[j]] = (uint16_t)(k[j] & 0xffffu);
-}
-
-// Value of lane 63 - lane of the wave (rows mirrored by DPP, then rows and
-// halves swapped).
-__device__ __forceinline__ uint32_t lane_rev(uint32_t x) {
-  const int lane = threadIdx.x & 63;
-  x = __builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true);     // row_mirror: lane ^ 15 in the row
-  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  x = (lane & 16) ? a[0] : a[1];
-  const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return (lane & 32) ? b[0] : b[1];
-}
-__device__ __forceinline__ double lane_rev(double x) {
-  const uint64_t v = (uint64_t)__double_as_longlong(x);
-  const uint32_t lo = lane_rev((uint32_t)v), hi = lane_rev((uint32_t)(v >> 32));
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-// One wave merges the positions [b0, b0 + 256) (clipped at N) whose two
-// halves [b0, b0 + 128) and [b0 + 128, b0 + 256) are each in order: four
-// keys per lane, the first stage compares position i with 255 - i (the
-// second half taken in reverse makes the block bitonic), then the seven
-// half-cleaning stages of a bitonic merge; written back as the new order of
-// these positions.  A block already in order is left alone.
-template <int NT>
-__device__ __forceinline__ void merge_block_wave(int b0, int N, int C, double iC, const double* kr,
-                                                 const uint16_t* ki, uint16_t* perm) {
-  const int lane = threadIdx.x & 63;
-  double r[4];
-  uint32_t k[4];
-  int sl[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int p = b0 + 4 * lane + j;
-    sl[j] = -1;
-    r[j] = INFINITY;
-    k[j] = 0xffffffffu;
-    if (p < N) {
-      sl[j] = pos_index<NT>(p, C, iC);
-      const unsigned src = perm[sl[j]];
-      r[j] = kr[src];
-      k[j] = ((uint32_t)ki[src] << 16) | src;
-    }
-  }
-  {
-    const double xr = lane_next(r[0]);
-    const uint32_t xk = lane_next(k[0]);
-    const bool ok = (lane == 63 || !pk_lt(xr, xk, r[3], k[3])) && !pk_lt(r[1], k[1], r[0], k[0]) &&
-                    !pk_lt(r[2], k[2], r[1], k[1]) && !pk_lt(r[3], k[3], r[2], k[2]);
-    if (__all(ok)) return;
-  }
-  // position 4 lane + j against 255 - (4 lane + j): lane 63 - lane, register 3 - j
-  {
-    double pr[4];
-    uint32_t pq[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { pr[j] = lane_rev(r[3 - j]); pq[j] = lane_rev(k[3 - j]); }
-    const bool lower = lane < 32;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (pk_lt(pr[j], pq[j], r[j], k[j]) == lower) { r[j] = pr[j]; k[j] = pq[j]; }
-  }
-#pragma unroll
-  for (int d = 64; d > 0; d >>= 1) {
-    if (d >= 4) {                   // partner in lane ^ (d / 4), same register
-      const int lm = d >> 2;
-      const bool lower = (lane & lm) == 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const double pr = lane_xor(r[j], lm);
-        const uint32_t pq = lane_xor(k[j], lm);
-        if (pk_lt(pr, pq, r[j], k[j]) == lower) { r[j] = pr; k[j] = pq; }
-      }
-    } else {                        // partner in this lane
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (j & d) continue;
-        const int jj = j | d;
-        if (pk_lt(r[jj], k[jj], r[j], k[j])) {
-          const double tr = r[j]; r[j] = r[jj]; r[jj] = tr;
-          const uint32_t tk = k[j]; k[j] = k[jj]; k[jj] = tk;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (sl[j] >= 0) perm[sl[j]] = (uint16_t)(k[j] & 0xffffu);
 }
 
 // Whether any of bits lo..hi (inclusive, lo <= hi) of a bit array is set.
@@ -972,7 +810,7 @@ __device__ __forceinline__ bool bits_any(const uint64_t* m, int lo, int hi) {
   return false;
 }
 
-// Key at position p through the order perm, as sort_block_wave compares them.
+// Key at position p through the order perm.
 template <int NT>
 __device__ __forceinline__ void key_at(int p, int C, double iC, const double* kr, const uint16_t* ki,
                                        const uint16_t* perm, double& r, uint32_t& k) {
@@ -990,14 +828,14 @@ __device__ __forceinline__ void key_at(int p, int C, double iC, const double* kr
 // of the second).  Up to two such rounds; returns whether the order is
 // complete (else the caller runs the general fix-up).
 //
-// dmask (optional): the push's disorder flags, bit t set if thread t's
-// chunk had a pair of positions out of order (inside it, or its last
-// position against the next chunk's first).  The first round then sorts
-// only the blocks of the first phase whose chunks flagged disorder (the
-// others are in order), only the blocks of the second phase over a junction
-// of the first phase's blocks left out of order, and checks the order at
-// the junctions of the second phase's blocks alone: every segment between
-// them is sorted, so the sequence is in order when they are.
+// dmask: the push's disorder flags, bit t set if thread t's chunk had a pair
+// of positions out of order (inside it, or its last position against the
+// next chunk's first).  The first round sorts only the blocks of the first
+// phase whose chunks flagged disorder (the others are in order), the second
+// all of them.  Of the second phase's blocks those over a junction of the
+// first phase's left out of order are merged, and the order is checked at
+// the second phase's junctions alone: every segment between them is sorted,
+// so the sequence is in order when they are.
 template <int NT>
 __device__ __noinline__ bool fix_order_blocks(const WakeInst& I, const double* kr, const uint16_t* ki,
                                               uint16_t* perm, const uint64_t* dmask) {
@@ -1006,90 +844,50 @@ __device__ __noinline__ bool fix_order_blocks(const WakeInst& I, const double* k
   const int wave = tid >> 6, lane = tid & 63;
   const int N = I.N, C = I.C;
   const double iC = 1.0 / (double)C;
-  const int p0 = tid * C;
-  const int cnt = max(0, min(C, N - p0));
+  const int cnt = max(0, min(C, N - tid * C));
   for (int k = 0; k < cnt; ++k) perm[k * NT + tid] = (uint16_t)(k * NT + tid);
   __syncthreads();
-  int round = 0;
-  if (dmask) {
-    round = 1;
-    // the first phase's blocks with flagged chunks, one block per lane
-    uint64_t bm;
-    {
-      const int b0 = lane << 8;
-      bm = __ballot(b0 < N && bits_any(dmask, b0 / C, min((b0 + 255) / C, NT - 1)));
-    }
+  // The callers are compiled knowing which registers this function leaves
+  // alone, and keep values there across the call; every slice of the march
+  // then pays for the spills that brings (1000 rings 12.0 us per slice against
+  // 11.8), a fix-up or not.  So it claims the scalar registers it does not use.
+  asm volatile("" ::: "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86",
+                      "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "s96", "s97", "s98", "s99",
+                      "s100", "s101");
+  // whether the positions before and after junction q are out of order
+  auto out = [&](int q) {
+    if (q >= N) return false;
+    double ra, rb;
+    uint32_t ka, kb;
+    key_at<NT>(q - 1, C, iC, kr, ki, perm, ra, ka);
+    key_at<NT>(q, C, iC, kr, ki, perm, rb, kb);
+    return pk_lt(rb, kb, ra, ka);
+  };
+  #pragma unroll 1
+  for (int round = 0; round < 2; ++round) {
+    // the first phase's blocks, one per lane
+    const int b0 = lane << 8;
+    uint64_t bm = __ballot(b0 < N && (round > 0 || bits_any(dmask, b0 / C, min((b0 + 255) / C, NT - 1))));
     int seen = 0;
     #pragma unroll 1
     while (bm) {
       const int b = __builtin_ctzll(bm);
       bm &= bm - 1;
-      if (seen++ % NW == wave) sort_block_wave<NT>(b * 256, N, C, iC, kr, ki, perm);
+      if (seen++ % NW == wave) sort_block_wave<NT, false>(b * 256, N, C, iC, kr, ki, perm);
     }
     __syncthreads();
-    // junctions q = 256 (j + 1) of the first phase's blocks, one per lane
-    bool out = false;
-    {
-      const int q = 256 * (lane + 1);
-      if (q < N) {
-        double ra, rb;
-        uint32_t ka, kb;
-        key_at<NT>(q - 1, C, iC, kr, ki, perm, ra, ka);
-        key_at<NT>(q, C, iC, kr, ki, perm, rb, kb);
-        out = pk_lt(rb, kb, ra, ka);
-      }
-    }
-    uint64_t jm = __ballot(out);
+    uint64_t jm = __ballot(out(256 * (lane + 1)));     // its junctions, one per lane
     seen = 0;
     #pragma unroll 1
     while (jm) {
       const int b = __builtin_ctzll(jm);
       jm &= jm - 1;
-      if (seen++ % NW == wave) merge_block_wave<NT>(128 + b * 256, N, C, iC, kr, ki, perm);
+      if (seen++ % NW == wave) sort_block_wave<NT, true>(128 + b * 256, N, C, iC, kr, ki, perm);
     }
     __syncthreads();
-    // junctions 128 + 256 j of the second phase's blocks
-    out = false;
-    {
-      const int q = 128 + 256 * lane;
-      if (q < N) {
-        double ra, rb;
-        uint32_t ka, kb;
-        key_at<NT>(q - 1, C, iC, kr, ki, perm, ra, ka);
-        key_at<NT>(q, C, iC, kr, ki, perm, rb, kb);
-        out = pk_lt(rb, kb, ra, ka);
-      }
-    }
-    if (!__ballot(out)) return true;     // the same keys in every wave: a uniform answer
+    // the same keys in every wave: a uniform answer
+    if (!__ballot(out(128 + 256 * lane))) return true;
     __syncthreads();                      // every wave has read the keys before a block moves
-  }
-  #pragma unroll 1
-  for (; round < 2; ++round) {
-    #pragma unroll 1
-    for (int b = wave; b * 256 < N; b += NW) sort_block_wave<NT>(b * 256, N, C, iC, kr, ki, perm);
-    __syncthreads();
-    #pragma unroll 1
-    for (int b = wave; 128 + b * 256 < N; b += NW) merge_block_wave<NT>(128 + b * 256, N, C, iC, kr, ki, perm);
-    __syncthreads();
-    // in order? (this chunk, and its last position against the next chunk's first)
-    int bad = 0;
-    if (cnt > 0) {
-      unsigned src = perm[tid];
-      double pr = kr[src];
-      uint32_t pq = ((uint32_t)ki[src] << 16) | src;
-      const int m = p0 + cnt < N ? cnt + 1 : cnt;
-      #pragma unroll 1
-      for (int k = 1; k < m; ++k) {
-        const unsigned sl = k < cnt ? k * NT + tid : tid + 1;
-        src = perm[sl];
-        const double r = kr[src];
-        const uint32_t q = ((uint32_t)ki[src] << 16) | src;
-        if (pk_lt(r, q, pr, pq)) bad = 1;
-        pr = r;
-        pq = q;
-      }
-    }
-    if (!__syncthreads_or(bad)) return true;
   }
   return false;
 }
