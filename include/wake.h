@@ -347,7 +347,7 @@ int wake_tiling_occupancy(int32_t threads, int32_t wgs_per_cu);
  * threads, with C = max(rings_per_thread, ceil(n_rings / (M threads)))
  * and G = ceil(n_rings / P) <= M, M = the smaller of 256 and the
  * workgroups of that size the device holds at once.  Per slice the members exchange their
- * scan totals through device memory (three all-gathers) and fix the ring
+ * scan totals through device memory (two all-gathers) and fix the ring
  * order on keys in device memory; the order is the same and the fields
  * agree with a single workgroup's to rounding.  The members of one instance
  * must be resident together: launches always place at least G workgroups.
