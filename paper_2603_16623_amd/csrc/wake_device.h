@@ -315,9 +315,9 @@ __device__ __forceinline__ double lane_prev_inf(double x) {
 // positions), so the networks compare radii alone, one instruction where
 // (radius, id) took three and two scalar ones on the path to each exchange;
 // rings of equal radius, which hardly occur, are put in the order of their
-// ids afterwards.  Sorting network 2300 -> 1500 instructions, merge 650 ->
-// 400; 7900 rings once they cross 87.2 -> 80.3 us per slice, 20000 rings on 5
-// members 57 -> 52, on 40 members 32.0 -> 29.0, 4000 rings of two species
+// ids afterwards.  The sort of a block in LDS 2457 -> 1795 instructions, a
+// merge 699; 7900 rings once they cross 87.2 -> 80.3 us per slice, 20000 rings
+// on 5 members 57 -> 52, on 40 members 32.0 -> 29.0, 4000 rings of two species
 // 82.5 -> 78.7.
 // Exchanges go by lane masks in scalar registers: left to itself the compiler
 // made branches of them, or masks of vector registers.
