@@ -877,6 +877,7 @@ __device__ __noinline__ bool fix_order_blocks(const WakeInst& I, const double* k
     }
     __syncthreads();
     uint64_t jm = __ballot(out(256 * (lane + 1)));     // its junctions, one per lane
+    __syncthreads();     // a merge moves the keys at its junction: every wave has read them, so all share the same jm
     seen = 0;
     #pragma unroll 1
     while (jm) {
