@@ -51,14 +51,12 @@ __device__ __forceinline__ Pack<4> mat_adj(const Pack<4>& m) {
   return {{m.v[3], -m.v[1], -m.v[2], m.v[0]}};
 }
 
-// a / b for double-double a with a precomputed reciprocal ib = 1/b: the
-// remainder of the first quotient comes from one fma (a.hi - q1 b is a
-// multiple of ulp(q1) ulp(b) of at most two ulps of q1 times b, so the fma
-// leaves it to within 2^-105 of a.hi), the second quotient takes it and a.lo.
+// a / b for double-double a with a precomputed reciprocal ib = 1/b
 __device__ __forceinline__ dd dd_div_rcp(dd a, double b, double ib) {
   _Pragma("clang fp contract(off)")
   const double q1 = a.hi * ib;
-  const double q2 = (__builtin_fma(-q1, b, a.hi) + a.lo) * ib;
+  const dd r = dd_sub(a, two_prod(q1, b));
+  const double q2 = r.hi * ib;
   return fast_two_sum(q1, q2);
 }
 
