@@ -14,6 +14,7 @@
 #include "../../include/wake.h"
 #include "wake_common.h"
 #include "wake_launch.h"
+#include "wake_rows.h"
 #include "wake_runtime.h"
 
 namespace {
@@ -770,20 +771,58 @@ static int copy_out(double* dst, const double* src, size_t n, int dev, hipStream
   return WAKE_OK;
 }
 
+// Whether the read-out kernels may write n doubles to each of outs
+// (wake_rows.h), from what the runtime knows of the pointers (rows <= OUT_N).
+static bool outs_by_kernel(const wake_ctx* c, double* const* outs, int rows, size_t n) {
+  OutMem mem[OUT_N];
+  for (int q = 0; q < rows; ++q) {
+    mem[q] = {0, 0, -1};
+    if (!outs[q]) continue;
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, outs[q]) == hipSuccess && a.type == hipMemoryTypeDevice &&
+        hipMemGetAddressRange(&base, &size, outs[q]) == hipSuccess)
+      mem[q] = {reinterpret_cast<uintptr_t>(base), size, a.device};
+    else
+      (void)hipGetLastError();     // a pointer it does not know: not an error of this call
+  }
+  return rows_by_kernel(outs, mem, rows, n, c->device);
+}
+
+// The context's device for a kernel launch, the caller's again after it (a
+// copy on the stream needs neither).
+struct OnDevice {
+  int prev = -1;
+  hipError_t e;
+  explicit OnDevice(int dev) {
+    e = hipGetDevice(&prev);
+    if (e == hipSuccess && prev != dev) e = hipSetDevice(dev);
+    else prev = -1;
+  }
+  ~OnDevice() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+};
+
 // Rows q (N doubles each, one after the other at base) to outs[q], null ones
-// skipped.  Device memory: one kernel.  Host memory: one transfer of all rows
+// skipped.  Device memory: one kernel where it may write them, else a copy per
+// row.  Host memory: one transfer of all rows
 // and a host copy each while they are short (a transfer to pageable memory
 // costs some 10 us whatever its size: six of them were most of a small solve's
 // read-out), a transfer per row beyond.
 static const size_t kRowsOnce = 8192;
-static int read_rows(const double* base, size_t N, double* const* outs, int rows, int dev, hipStream_t s) {
-  if (dev) {
+static int read_rows(const wake_ctx* c, const double* base, size_t N, double* const* outs, int rows, int dev) {
+  const hipStream_t s = c->stream;
+  if (dev && outs_by_kernel(c, outs, rows, N)) {
+    const OnDevice d(c->device);
+    HIP_TRY(d.e);
     HIP_TRY(launch_rows_out(base, N, outs, rows, s));
     return WAKE_OK;
   }
   int wanted = 0;
   for (int q = 0; q < rows; ++q) wanted += outs[q] != nullptr;
-  double* tmp = N <= kRowsOnce && wanted > 1 ? new (std::nothrow) double[N * rows] : nullptr;
+  double* tmp = !dev && N <= kRowsOnce && wanted > 1 ? new (std::nothrow) double[N * rows] : nullptr;
   if (tmp) {
     hipError_t e = hipMemcpyAsync(tmp, base, sizeof(double) * N * rows, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -823,7 +862,7 @@ static int fields_of(wake_ctx* c, const double* snap, const double* last, int32_
   }
   const size_t N = I.N;
   double* outs[OUT_N] = {psi, erbt, ez, bt, rho, ur};
-  r = read_rows(base, N, outs, OUT_N, dev, c->stream);
+  r = read_rows(c, base, N, outs, OUT_N, dev);
   if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return WAKE_OK;
@@ -1055,7 +1094,7 @@ extern "C" int wake_grid_fields(wake_ctx* c, int32_t slice, double* psi, double*
   grid_slice(c, slice, &first, &ng);
   const double* base = I.grid + 5 * first;
   double* outs[4] = {psi, erbt, ez, bt};
-  r = read_rows(base, ng, outs, 4, dev, c->stream);
+  r = read_rows(c, base, ng, outs, 4, dev);
   if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return WAKE_OK;
@@ -1096,7 +1135,7 @@ extern "C" int wake_grid_chi(wake_ctx* c, int32_t slice, double* chi, int32_t de
 }
 
 // The axis values sit on the device as (psi, E_z) pairs per slice: split by a
-// kernel (device memory) or on the host after one transfer.  (Two strided
+// kernel (device memory it may write) or on the host after one transfer.  (Two strided
 // copies of 8-B rows took 7 us a row and copy: 16 ms for 1200 slices, as long
 // as a 1000-ring march through them; the transfer and the split take 30 us.)
 extern "C" int wake_lineout(wake_ctx* c, double* psi_axis, double* ez_axis, int32_t dev) {
@@ -1106,7 +1145,17 @@ extern "C" int wake_lineout(wake_ctx* c, double* psi_axis, double* ez_axis, int3
   const size_t n = c->I.n_xi;
   if (!psi_axis && !ez_axis) return WAKE_OK;
   if (dev) {
-    HIP_TRY(launch_axis_out(c->I.axis, n, psi_axis, ez_axis, c->stream));
+    double* outs[2] = {psi_axis, ez_axis};
+    if (outs_by_kernel(c, outs, 2, n)) {
+      const OnDevice d(c->device);
+      HIP_TRY(d.e);
+      HIP_TRY(launch_axis_out(c->I.axis, n, psi_axis, ez_axis, c->stream));
+    } else {
+      for (int q = 0; q < 2; ++q)
+        if (outs[q])
+          HIP_TRY(hipMemcpy2DAsync(outs[q], sizeof(double), c->I.axis + q, 2 * sizeof(double), sizeof(double), n,
+                                   hipMemcpyDeviceToDevice, c->stream));
+    }
     HIP_TRY(hipStreamSynchronize(c->stream));
     return WAKE_OK;
   }
@@ -1139,7 +1188,7 @@ static int get_state_of(wake_ctx* c, int sp, int32_t* slice, double* rho, double
   else
     HIP_TRY(launch_state_by_id(c->I, st, st + N, st + 2 * N, st + 3 * N, c->stream));
   double* outs[4] = {rho, ur, f_rho, f_u};
-  r = read_rows(st, N, outs, 4, dev, c->stream);
+  r = read_rows(c, st, N, outs, 4, dev);
   if (r != WAKE_OK) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (slice) *slice = next;

@@ -80,3 +80,39 @@ def test_host_and_device_readouts_agree(n_rings):
     assert lib.wake_lineout(s.h, None, only.ctypes.data, 0) == 0
     assert np.array_equal(only, ez)
     s.close()
+
+
+def test_device_outputs_that_share_memory_take_the_last_row():
+    """The same device buffer for several outputs: the rows arrive in order,
+    the last one whole (copies on the stream, not one kernel's stores)."""
+    from paper_2603_16623_amd import wake as wk
+    lib = wk.load()
+    wk.wake_set_tiling(512, 0)
+    wk.wake_set_cluster(0, 0)
+    n = 5000
+    inst = W.small_instance(21, n_rings=n, n_xi=300, n_peak=2.0, dxi=0.01, geometric=False)
+    s = wk.WakeSolver.from_instance(inst)
+    s.wake_set_grid(700, 2.0)
+    s.wake_solve()
+    hip = _hip_runtime()
+    h, g, st = s.wake_fields(-1), s.wake_grid_fields(-1), s.wake_get_state()
+    b = _Buf(hip, n)
+    s.wake_fields(-1, out={k: b for k in h}, device=True)
+    assert np.array_equal(b.host(), h["ur"])
+    b = _Buf(hip, 2 * n)                    # two outputs half over one another
+    p = b.data_ptr()
+    assert lib.wake_fields(s.h, -1, p, p + 8 * (n // 2), None, None, None, None, 1) == 0
+    got = b.host()
+    assert np.array_equal(got[:n // 2], h["psi"][:n // 2])
+    assert np.array_equal(got[n // 2:n // 2 + n], h["er_bt"])
+    b = _Buf(hip, 700)
+    s.wake_grid_fields(-1, out={k: b for k in g}, device=True)
+    assert np.array_equal(b.host(), g["bt"])
+    b = _Buf(hip, n)
+    assert lib.wake_get_state(s.h, None, b.data_ptr(), b.data_ptr(), None, None, 1) == 0
+    assert np.array_equal(b.host(), st["ur"])
+    psi, ez = s.wake_lineout()
+    b = _Buf(hip, inst.n_xi)
+    assert lib.wake_lineout(s.h, b.data_ptr(), b.data_ptr(), 1) == 0
+    assert np.array_equal(b.host(), ez)
+    s.close()
