@@ -807,11 +807,14 @@ struct OnDevice {
 
 // Rows q (N doubles each, one after the other at base) to outs[q], null ones
 // skipped.  Device memory: one kernel where it may write them, else a copy per
-// row.  Host memory: one transfer of all rows
-// and a host copy each while they are short (a transfer to pageable memory
-// costs some 10 us whatever its size: six of them were most of a small solve's
-// read-out), a transfer per row beyond.
-static const size_t kRowsOnce = 8192;
+// row.  Host memory: one transfer of all rows and a host copy each while they
+// are short (a transfer to pageable memory costs some 10 us whatever its size:
+// six of them were most of a small solve's read-out), a transfer per row
+// beyond.  wake_fields, all rows at once against a transfer each: all six 27 / 96
+// us at 500 rings, 46 / 80 at 8192, 69 / 100 at 16384, 141 / 132 at 32768; two of
+// the six, the other four moved in vain, 27 / 47 at 2000, 31.5 / 32.5 at 4096,
+// 39 / 36 at 8192.  So at most 2048 elements a row for each row wanted.
+static const size_t kRowsOnce = 8192, kRowsOnceEach = 2048;
 static int read_rows(const wake_ctx* c, const double* base, size_t N, double* const* outs, int rows, int dev) {
   const hipStream_t s = c->stream;
   if (dev && outs_by_kernel(c, outs, rows, N)) {
@@ -822,7 +825,8 @@ static int read_rows(const wake_ctx* c, const double* base, size_t N, double* co
   }
   int wanted = 0;
   for (int q = 0; q < rows; ++q) wanted += outs[q] != nullptr;
-  double* tmp = !dev && N <= kRowsOnce && wanted > 1 ? new (std::nothrow) double[N * rows] : nullptr;
+  const bool once = !dev && wanted > 1 && N <= std::min(kRowsOnce, kRowsOnceEach * wanted);
+  double* tmp = once ? new (std::nothrow) double[N * rows] : nullptr;
   if (tmp) {
     hipError_t e = hipMemcpyAsync(tmp, base, sizeof(double) * N * rows, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

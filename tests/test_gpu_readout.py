@@ -116,3 +116,21 @@ def test_device_outputs_that_share_memory_take_the_last_row():
     assert lib.wake_lineout(s.h, b.data_ptr(), b.data_ptr(), 1) == 0
     assert np.array_equal(b.host(), ez)
     s.close()
+
+
+# two and three of six rows: at once up to 4096 and 6144 rings, a transfer each beyond
+@pytest.mark.parametrize("n_rings", [4096, 4097, 6144, 6145])
+def test_some_rows_into_host_memory(n_rings):
+    from paper_2603_16623_amd import wake as wk
+    wk.load()
+    wk.wake_set_tiling(512, 0)
+    wk.wake_set_cluster(0, 0)
+    s = wk.WakeSolver.from_instance(W.small_instance(21, n_rings=n_rings, n_xi=4, n_peak=2.0, dxi=0.1, geometric=False))
+    s.wake_solve()
+    whole = s.wake_fields(-1)
+    for names in (("psi", "ur"), ("er_bt", "bt"), ("psi", "ez", "rho")):
+        some = {k: np.full(n_rings, np.nan) for k in names}
+        s.wake_fields(-1, out=some)
+        for k in names:
+            assert np.array_equal(some[k], whole[k]), (names, k)
+    s.close()
