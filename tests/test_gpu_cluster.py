@@ -300,3 +300,47 @@ def test_cluster_fixups_in_device_memory(wk, u_amp):
     check_fields(got, ref, field_scales(ref), label)
     assert np.array_equal(got["rho"], mid_dev["rho"])
     s.close()
+
+
+@pytest.mark.parametrize("shift", [0.3, -0.3])
+def test_cluster_interval_window_follows_the_rings(wk, shift):
+    """Members of four rings per thread keep a window of 4097 ion-interval
+    nodes around their rings: with a column stretched or squeezed by 2400
+    nodes the rings of most members lie outside the window a launch starts
+    with, which moves after the launch's first slice.  Three slices in one
+    launch equal, bitwise, a launch each (every window where it starts), and
+    the last matches the oracle on the device's state; members at both ends of
+    the table among them."""
+    inst = W.small_instance(8, n_rings=24000, n_xi=20, n_peak=3.0, sigma_r=0.2, geometric=False, dxi=0.02)
+    o = _oracle(inst)
+    state = o.initial_state()
+    state["rho"] = inst.r0 + shift * np.sin(np.pi * inst.r0 / 3.0)
+    wk.wake_set_tiling(256, 0)
+    wk.wake_set_cluster(4, 500)
+    n = 8
+    label = f"cluster interval window shift={shift}"
+    _say(label)
+    each = wk.WakeSolver.from_instance(inst, record_stride=1)
+    assert each.layout() == (24, 4)
+    each.wake_set_state(n, state["rho"], state["u"], state["fr"], state["fu"])
+    for m in range(3):
+        if m == 2:
+            mid = each.wake_get_state()
+        each.wake_solve(n + m, 1)
+    want = [each.wake_fields(n + m) for m in range(3)]
+    end = each.wake_get_state()
+    each.close()
+    s = wk.WakeSolver.from_instance(inst, record_stride=1)
+    s.wake_set_state(n, state["rho"], state["u"], state["fr"], state["fu"])
+    s.wake_solve(n, 3)
+    assert s.wake_status()[0] == -1
+    for m in range(3):
+        got = s.wake_fields(n + m)
+        for q in FIELDS + ("rho",):
+            assert np.array_equal(got[q], want[m][q]), (m, q)
+    st = s.wake_get_state()
+    for q in ("rho", "ur", "f_rho", "f_u"):
+        assert np.array_equal(st[q], end[q]), q
+    ref, _ = o.slice(n + 2, dict(rho=mid["rho"], u=mid["ur"], fr=mid["f_rho"], fu=mid["f_u"]), keep=True)
+    check_fields(got, ref, field_scales(ref), label)
+    s.close()
