@@ -29,9 +29,9 @@
 //                     ring i and J s = (s_b, -s_a), split as lambda0 +
 //                     c lambda1 because s_i is affine in the one unknown
 //                     c = -(v of this chunk and every later one).
-//   scan              prefix of (G, v) (g at the chunk start), suffix of
-//                     (G^-1, v) (h at the chunk end).  The chunk's sums are
-//                     then det-sums without another pass:
+//   scan              prefix of G (g at the chunk start), suffix of (G^-1, v)
+//                     (h at the chunk end; v after the chunk, and its total).
+//                     The chunk's sums are then det-sums without another pass:
 //                     sum det[g_i, s_i] = g_start . lambda,
 //                     sum det[s_i, h_i] = -(G^-1 h_end) . lambda.
 //   scan              prefix of the det[g, s] sums, suffix of det[s, h].
@@ -1605,7 +1605,9 @@ __device__ __forceinline__ void march(const WakeInst& I, int member, const int32
   // interval at the previous slice, made the slowest member late.  Eight
   // rings per thread: 20000 rings on 5 members 57.1 -> 54.5 us per slice
   // once the rings moved (39.0 -> 39.6 while they rest), 200000 on 49
-  // 55.0 -> 52.8, 40 served requests 191 -> 182 ms.  With one or two rings
+  // 55.0 -> 52.8, 40 served requests 191 -> 182 ms; four per thread, 20000
+  // rings 33.7 -> 33.0 and 200000 41.3 -> 40.3, three 30.6 -> 30.2 and 37.8 ->
+  // 37.6.  With one or two rings
   // per thread that interval comes with the ring, whose record's load need
   // not wait for a search (20000 rings on 40 members 19.2 us per slice, 20.0
   // with the window); a variant of its own, since the window's scalars alone
