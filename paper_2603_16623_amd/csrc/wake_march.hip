@@ -849,8 +849,10 @@ __device__ __noinline__ bool fix_order_blocks(const WakeInst& I, const double* k
   __syncthreads();
   // The callers are compiled knowing which registers this function leaves
   // alone, and keep values there across the call; every slice of the march
-  // then pays for the spills that brings (1000 rings 12.0 us per slice against
-  // 11.8), a fix-up or not.  So it claims the scalar registers it does not use.
+  // then pays for the spills that brings, a fix-up or not.  So it claims the
+  // scalar registers it does not use.  With this compiler, without the claim and
+  // with it: 96 rings 7.6 and 7.25 us per slice, 1000 rings 11.97 and 11.7, 1500
+  // 20.1 and 20.05; 7900 rings 80.2 and 81.2, the batch of 512 95.8 and 96.2 ms.
   asm volatile("" ::: "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86",
                       "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "s96", "s97", "s98", "s99",
                       "s100", "s101");
@@ -877,7 +879,10 @@ __device__ __noinline__ bool fix_order_blocks(const WakeInst& I, const double* k
     }
     __syncthreads();
     uint64_t jm = __ballot(out(256 * (lane + 1)));     // its junctions, one per lane
-    __syncthreads();     // a merge moves the keys at its junction: every wave has read them, so all share the same jm
+    // a merge moves the keys at its junction: the barrier lets every wave read
+    // them first, so that all have the same list (7900 rings 80.3 -> 81.2 us per
+    // slice, the others unchanged)
+    __syncthreads();
     seen = 0;
     #pragma unroll 1
     while (jm) {
